@@ -82,8 +82,8 @@ __device__ __forceinline__ void osher(int k, const R *qL, const R *qR, R *G, R g
 }
 
 // The scheme's numerical flux (Sec. 2.3): Rusanov or Osher-type.
-template <int DIM, typename R>
-__device__ __forceinline__ void num_flux(const Prob &P, const Tables *T, int k, const R *qL, const R *qR, R *G) {
+template <int DIM, typename R, typename TP>
+__device__ __forceinline__ void num_flux(const Prob &P, TP T, int k, const R *qL, const R *qR, R *G) {
     if (P.flux == 1) {
         R xs[3], ws[3];
 #pragma unroll

@@ -38,6 +38,10 @@ struct Tables {
     float fD3[3][3], fKw3[3][3], fL3[3], fR3[3], fw3[3], fxi3[3];
 };
 
+// The tables in the constant address space (they do not change while a kernel runs): uniform
+// entries come through scalar loads wherever they are read.
+typedef const Tables __attribute__((address_space(4))) *TabC;
+
 struct BCDev {
     int kind[2];
     int split_axis;

@@ -374,8 +374,8 @@ __device__ __forceinline__ void store_cell_bounds(const Prob &P, const Bufs &B, 
 // NI (input).  One thread owns one line along axis k: it loads the NI inputs of its line
 // once and produces the M outputs.  The operator entries are the same for every lane, so
 // they are read from the table in global memory through scalar loads, not from LDS.
-template <int DIM, int K, int M, int NI, int NVAR, int MSTRIDE>
-__device__ __forceinline__ void tensor_stage(const double *__restrict__ Mat, const double *src, double *dst, int tid,
+template <int DIM, int K, int M, int NI, int NVAR, int MSTRIDE, typename MP>
+__device__ __forceinline__ void tensor_stage(MP Mat, const double *src, double *dst, int tid,
                                              int bs) {
     constexpr int S0 = (0 < K) ? M : NI, S1 = (1 < K) ? M : NI, S2 = (DIM == 3) ? ((2 < K) ? M : NI) : 1;
     constexpr int IS[3] = {1, S0, S0 * S1};                               // input strides
@@ -408,8 +408,8 @@ __device__ __forceinline__ void tensor_stage(const double *__restrict__ Mat, con
     __syncthreads();
 }
 
-template <int DIM, int M, int NI, int NVAR, int MSTRIDE>
-__device__ __forceinline__ void tensor_apply(const double *__restrict__ Mbase, const double *in, double *out, double *tmp, int tid,
+template <int DIM, int M, int NI, int NVAR, int MSTRIDE, typename MP>
+__device__ __forceinline__ void tensor_apply(MP Mbase, const double *in, double *out, double *tmp, int tid,
                              int bs) {
     // the buffers alternate so that the last stage lands in `out`
     if constexpr (DIM == 2) {
@@ -981,8 +981,8 @@ __device__ __forceinline__ void position_coords(int pos, int Ns, int *L) {
 // (the cell, its neighbours, or the interior cells a non-periodic ghost mirrors) have their
 // DG coefficients staged in LDS first (nbu, 3^d x NV x n^d values; null: read from HBM).
 template <int DIM, int N>
-__device__ __forceinline__ void sub_halo_cell(const Tables *__restrict__ T, const Prob &P, const Bufs &B, int cur, int w,
-                              double *halo, double *nbu) {
+__device__ __forceinline__ void sub_halo_cell(TabC T, const Prob &P, const Bufs &B, int cur, int w,
+                              double *halo, double *nbu, int tid) {
     constexpr int n = N + 1, NV = DIM + 2, NN = cpow(n, DIM);
     constexpr int NS = 2 * N + 1, NSUB = cpow(NS, DIM), HN = NS + 6, HSZ = cpow(HN, DIM), NB = cpow(3, DIM);
     const int64_t c = B.tlist[w];
@@ -1010,7 +1010,7 @@ __device__ __forceinline__ void sub_halo_cell(const Tables *__restrict__ T, cons
         }
     };
     if (nbu) {
-        for (int i = threadIdx.x; i < NB * NV * NN; i += blockDim.x) {
+        for (int i = tid; i < NB * NV * NN; i += SUB_BS) {
             const int o = i / (NV * NN), v = (i / NN) % NV, a = i % NN;
             int gci[3] = {0, 0, 0};
             for (int j = 0, r = o; j < DIM; j++, r /= 3) gci[j] = ci[j] + r % 3 - 1;
@@ -1020,7 +1020,7 @@ __device__ __forceinline__ void sub_halo_cell(const Tables *__restrict__ T, cons
         }
         __syncthreads();
     }
-    for (int hidx = threadIdx.x; hidx < HSZ; hidx += blockDim.x) {
+    for (int hidx = tid; hidx < HSZ; hidx += SUB_BS) {
         int hl[3] = {hidx % HN, (hidx / HN) % HN, hidx / (HN * HN)};
         int off[3] = {0, 0, 0}, gs[3] = {0, 0, 0}, ss[3] = {0, 0, 0};
         for (int j = 0; j < DIM; j++) {
@@ -1056,20 +1056,28 @@ __device__ __forceinline__ void sub_halo_cell(const Tables *__restrict__ T, cons
 #pragma unroll
             for (int v = 0; v < NV; v++) q[v] = B.pool[0][((int64_t)slot * NV + v) * NSUB + sidx];
         } else {
-            // P(u^n) at one subcell: plain tensor sum over the nodes
-            int o = 0;
-            for (int j = DIM - 1; j >= 0; j--) o = o * 3 + (off[j] + 1);
-            const double *nb = staged ? nbu : nullptr;
+            // P(u^n) at one subcell: the rows along x first, their sums along y
+            static_assert(DIM == 2, "3D halos go region by region");
+            double px[n];
 #pragma unroll
-            for (int v = 0; v < NV; v++) q[v] = 0.0;
-            for (int a = 0; a < NN; a++) {
-                int m[3] = {a % n, (a / n) % n, a / (n * n)};
-                double wgt = 1.0;
-                for (int j = 0; j < DIM; j++) wgt *= T->P[ss[j]][m[j]];
+            for (int m0 = 0; m0 < n; m0++) px[m0] = T->P[ss[0]][m0];
+            auto point = [&](const double *x, int64_t vstride) {
 #pragma unroll
-                for (int v = 0; v < NV; v++)
-                    q[v] += wgt * (nb ? nb[(o * NV + v) * NN + a] : B.u[cur][((int64_t)v * P.ncell + cs) * NN + a]);
-            }
+                for (int v = 0; v < NV; v++) q[v] = 0.0;
+#pragma unroll 1
+                for (int m1 = 0; m1 < n; m1++) {
+                    const double py = T->P[ss[1]][m1];
+#pragma unroll
+                    for (int v = 0; v < NV; v++) {
+                        double row = 0.0;
+#pragma unroll
+                        for (int m0 = 0; m0 < n; m0++) row += px[m0] * x[v * vstride + m1 * n + m0];
+                        q[v] += py * row;
+                    }
+                }
+            };
+            if (staged) point(nbu + ((off[1] + 1) * 3 + off[0] + 1) * NV * NN, NN);
+            else point(B.u[cur] + cs * NN, P.ncell * NN);
         }
         double x[3] = {0, 0, 0};
         for (int j = 0; j < DIM; j++) x[j] = P.lo[j] + P.h[j] * (gci[j] + (gs[j] + 0.5) / NS);
@@ -1098,8 +1106,8 @@ __device__ __forceinline__ void sub_halo_cell(const Tables *__restrict__ T, cons
 // cell troubled at the previous step gives its stored subcell data instead.  st: scratch of
 // NV (NS n^2 + NS^2 n) doubles for the first two stages.
 template <int N>
-__device__ __forceinline__ void sub_halo_cell3(const Tables *__restrict__ T, const Prob &P, const Bufs &B, int cur, int w,
-                                               double *halo, double *st) {
+__device__ __forceinline__ void sub_halo_cell3(TabC T, const Prob &P, const Bufs &B, int cur, int w,
+                                               double *halo, double *st, int tid) {
     constexpr int DIM = 3, n = N + 1, NV = 5, NN = n * n * n;
     constexpr int NS = 2 * N + 1, NSUB = NS * NS * NS, HN = NS + 6, HSZ = HN * HN * HN;
     double *st1 = st, *st2 = st + NV * NS * n * n;
@@ -1158,10 +1166,10 @@ __device__ __forceinline__ void sub_halo_cell3(const Tables *__restrict__ T, con
         if (!pooled) {
             // stage 1 (x): st1[v][i0][a2][a1] = sum_a0 P[sslo0 + i0][a0] u[v][a0, a1, a2]
             const int n1 = NV * gn[0] * n * n;
-            for (int it = threadIdx.x; it < n1; it += blockDim.x) {
+            for (int it = tid; it < n1; it += SUB_BS) {
                 const int a12 = it % (n * n), i0 = (it / (n * n)) % gn[0], v = it / (n * n * gn[0]);
                 const double *x = u + ((int64_t)v * P.ncell + cs) * NN + a12 * n;
-                const double *pr = T->P[sslo[0] + i0];
+                const auto *pr = T->P[sslo[0] + i0];
                 double acc = 0.0;
 #pragma unroll
                 for (int a0 = 0; a0 < n; a0++) acc += pr[a0] * x[a0];
@@ -1170,10 +1178,10 @@ __device__ __forceinline__ void sub_halo_cell3(const Tables *__restrict__ T, con
             __syncthreads();
             // stage 2 (y): st2[v][i0][i1][a2] = sum_a1 P[sslo1 + i1][a1] st1[v][i0][a2][a1]
             const int n2 = NV * gn[0] * gn[1] * n;
-            for (int it = threadIdx.x; it < n2; it += blockDim.x) {
+            for (int it = tid; it < n2; it += SUB_BS) {
                 const int a2 = it % n, i1 = (it / n) % gn[1], vi0 = it / (n * gn[1]);   // vi0 = v * gn0 + i0
                 const double *x = st1 + ((int64_t)vi0 * n + a2) * n;     // st1[v][i0][a2][a1], a1 fastest
-                const double *pr = T->P[sslo[1] + i1];
+                const auto *pr = T->P[sslo[1] + i1];
                 double acc = 0.0;
 #pragma unroll
                 for (int a1 = 0; a1 < n; a1++) acc += pr[a1] * x[a1];
@@ -1183,7 +1191,7 @@ __device__ __forceinline__ void sub_halo_cell3(const Tables *__restrict__ T, con
         }
         // stage 3 (z) per halo point of the region, all variables, then the boundary rules
         const int np = gn[0] * gn[1] * gn[2];
-        for (int it = threadIdx.x; it < np; it += blockDim.x) {
+        for (int it = tid; it < np; it += SUB_BS) {
             const int i[3] = {it % gn[0], (it / gn[0]) % gn[1], it / (gn[0] * gn[1])};
             int ss[3], gsI[3], hl[3];
 #pragma unroll
@@ -1199,7 +1207,7 @@ __device__ __forceinline__ void sub_halo_cell3(const Tables *__restrict__ T, con
 #pragma unroll
                 for (int v = 0; v < NV; v++) q[v] = B.pool[0][((int64_t)slot * NV + v) * NSUB + sidx];
             } else {
-                const double *pr = T->P[ss[2]];
+                const auto *pr = T->P[ss[2]];
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
                     const double *x = st2 + (((int64_t)v * gn[0] + i[0]) * gn[1] + i[1]) * n;
@@ -1233,7 +1241,7 @@ __device__ __forceinline__ void sub_halo_cell3(const Tables *__restrict__ T, con
 
 // One-dimensional WENO3 (degree 2, three stencils, lambda = 1, 1e5, 1, eps 1e-14, r 8):
 // five averages at offsets -2..2 -> values at the three GL nodes of the central subcell.
-__device__ __forceinline__ void weno3(const Tables *__restrict__ T, const double *a, double *out) {
+__device__ __forceinline__ void weno3(TabC T, const double *a, double *out) {
     double c[3][3], wt[3], sum = 0.0;
     const double lam[3] = {1.0, 1.0e5, 1.0};
 #pragma unroll
@@ -1268,7 +1276,7 @@ __device__ __forceinline__ void weno3(const Tables *__restrict__ T, const double
 // lambda_k ((sigma_min + eps) / (sigma_k + eps))^8 before normalisation, so that they stay in
 // FP32 range (the unscaled (sigma + eps)^-8 overflows for eps = 1e-14); reciprocals by the
 // hardware reciprocal.
-__device__ __forceinline__ void weno3(const Tables *__restrict__ T, const float *a, float *out) {
+__device__ __forceinline__ void weno3(TabC T, const float *a, float *out) {
     float c[3][3], sg[3];
     const float lam[3] = {1.0f, 1.0e5f, 1.0f};
 #pragma unroll
@@ -1308,13 +1316,14 @@ __device__ __forceinline__ void weno3(const Tables *__restrict__ T, const float 
 // the 3^d GL points of the subcell (x sweep on the averages, then y (then z) sweeps on
 // the nodal values of the previous sweep).  One work item per (position, variable).
 template <int DIM, int N, typename R>
-__device__ __forceinline__ void sub_recon_cell(const Tables *__restrict__ T, double *Yscratch, int sidx, const double *halo,
-                                               R *stg) {
+__device__ __forceinline__ void sub_recon_cell(TabC T, double *Yscratch, int sidx, const double *halo,
+                                               R *stg, int tid) {
     constexpr int NV = DIM + 2, NS = 2 * N + 1, HN = NS + 6, HSZ = cpow(HN, DIM);
     constexpr int NPOS = cpow(NS, DIM) + 2 * DIM * cpow(NS, DIM - 1), N3 = cpow(3, DIM);
     if constexpr (DIM == 2) {
         (void)stg;
-        for (int item = threadIdx.x; item < NPOS * NV; item += blockDim.x) {
+#pragma unroll 1
+        for (int item = tid; item < NPOS * NV; item += SUB_BS) {
             const int v = item / NPOS, pos = item % NPOS;
             int L[3];
             position_coords<DIM>(pos, NS, L);
@@ -1350,7 +1359,7 @@ __device__ __forceinline__ void sub_recon_cell(const Tables *__restrict__ T, dou
                       "the sweeps' intermediates must fit the slot's trace storage");
         R *vx = stg;                                           // [v][i][kh][jh][qx]
         R *vxy = stg + (int64_t)NV * NI * HN * HN * 3;         // [v][i][j][kh][qy][qx]
-        for (int it = threadIdx.x; it < NV * NI * HN * HN; it += blockDim.x) {
+        for (int it = tid; it < NV * NI * HN * HN; it += SUB_BS) {
             const int jh = it % HN, kh = (it / HN) % HN, i = (it / (HN * HN)) % NI, v = it / (HN * HN * NI);
             const double *h = halo + (int64_t)v * HSZ + (kh * HN + jh) * HN + i;
             R a5[5], o3[3];
@@ -1361,7 +1370,7 @@ __device__ __forceinline__ void sub_recon_cell(const Tables *__restrict__ T, dou
             for (int q = 0; q < 3; q++) vx[(int64_t)it * 3 + q] = o3[q];
         }
         __syncthreads();
-        for (int it = threadIdx.x; it < NV * NI * NI * HN * 3; it += blockDim.x) {
+        for (int it = tid; it < NV * NI * NI * HN * 3; it += SUB_BS) {
             const int qx = it % 3, kh = (it / 3) % HN, j = (it / (3 * HN)) % NI;
             const int i = (it / (3 * HN * NI)) % NI, v = it / (3 * HN * NI * NI);
             const R *src = vx + ((((int64_t)v * NI + i) * HN + kh) * HN + j) * 3 + qx;
@@ -1374,7 +1383,7 @@ __device__ __forceinline__ void sub_recon_cell(const Tables *__restrict__ T, dou
             for (int qy = 0; qy < 3; qy++) dst[qy * 3] = o3[qy];
         }
         __syncthreads();
-        for (int it = threadIdx.x; it < NPOS * NV * 9; it += blockDim.x) {
+        for (int it = tid; it < NPOS * NV * 9; it += SUB_BS) {
             const int qq = it % 9, item = it / 9;
             const int v = item / NPOS, pos = item % NPOS;
             int L[3];
@@ -1391,26 +1400,64 @@ __device__ __forceinline__ void sub_recon_cell(const Tables *__restrict__ T, dou
     }
 }
 
+// Face traces of the subcell predictor in a workgroup's slot, ordered by sub-face: [axis k][side of
+// the sub-face: 0 left, 1 right][v][time node][sub-face f * Ns^(d-1) + tangential subcell][tangential
+// node].  The sub-face fluxes read them with consecutive lanes on consecutive values.
+template <int DIM, int N>
+struct SubTrace {
+    static constexpr int NV = DIM + 2, NS = 2 * N + 1, NF3 = cpow(3, DIM - 1);
+    static constexpr int SF = (NS + 1) * cpow(NS, DIM - 1);   // sub-faces per axis
+    static constexpr int ROW = SF * NF3;                      // one variable at one time node
+    static __device__ __forceinline__ int64_t at(int k, int right, int v, int s) {
+        return (int64_t)(((k * 2 + right) * NV + v) * 3 + s) * ROW;
+    }
+    static constexpr int64_t SIZE = (int64_t)DIM * 2 * NV * 3 * ROW;
+};
+
+// Exchange rows of the subcell predictor: NV x 3 values per lane, padded so that the 16-byte
+// accesses of eight consecutive lanes fall into different LDS banks (row strides of 20 and 12
+// dwords in FP32, 36 and 28 in FP64, for d = 3 and 2).
+template <int DIM, typename R>
+struct SubRow {
+    static constexpr int NVAL = (DIM + 2) * 3;
+    static constexpr int STRIDE = sizeof(R) == 4 ? (DIM == 3 ? 20 : 12) : (DIM == 3 ? 18 : 14);
+    static constexpr int BYTES = SUB_BS * STRIDE * (int)sizeof(R);   // every wave of the workgroup
+};
+
+// LDS block of the subcell recompute, taken in turn by the halo's staging (2D: the source cells'
+// coefficients; 3D: the stages of the sum-factorised P), the predictor's exchange rows and the
+// update (the sub-face fluxes, whose place the gather's intermediate stage and result take, and
+// the new subcell averages).  Large cells hold only the exchange rows here.
+template <int DIM, int N, typename R>
+struct SubLds {
+    static constexpr int n = N + 1, NV = DIM + 2, NS = 2 * N + 1, NN = cpow(n, DIM), NSUB = cpow(NS, DIM);
+    static constexpr int CELL = NV * (NSUB > NN ? NSUB : NN) * 8;                       // one cell's values
+    static constexpr int FB = DIM * (NS + 1) * cpow(NS, DIM - 1) * NV * (int)sizeof(R);  // sub-face fluxes
+    static constexpr int UG = CELL, VN = ((FB > 2 * CELL ? FB : 2 * CELL) + 15) / 16 * 16;
+    static constexpr int HALO = (DIM == 2 ? 9 * NV * NN : NV * NS * n * n + NV * NS * NS * n) * 8;
+    static constexpr int M1 = VN + CELL > HALO ? VN + CELL : HALO, ROWS = SubRow<DIM, R>::BYTES;
+    static constexpr int BYTES = BigCell<DIM, N>::on ? ROWS : (M1 > ROWS ? M1 : ROWS);
+};
+
 // S4: sub-face Rusanov fluxes, FV update, gather, pool store, boundary fluxes.
 // MOOD layer (Sec. 6, Fig. algo2): with flagging set, every subcell of the WENO3 result
 // that fails PAD or the relaxed DMP against this cell's bounds (mb) is flagged; REDO
 // recomputes with the first-order flux on every sub-face next to a flagged subcell (own
 // flags, or the face neighbour's, whose pool slot is in nslot).
 template <int DIM, int N, typename R, bool REDO>
-__device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, const Prob &P, const Bufs &B, int cur,
+__device__ __forceinline__ void sub_update_cell(TabC T, const Prob &P, const Bufs &B, int cur,
                                                 int w, int sidx, const SubScratch &S, int *nonphys, const double *halo,
                                                 int flagging,
                                                 const double (*mb)[DIM + 2], const int (*nslot)[2],
-                                                unsigned char *fbt) {
+                                                unsigned char *scr, int tid) {
     constexpr int n = N + 1, NV = DIM + 2, NN = cpow(n, DIM);
     constexpr int NS = 2 * N + 1, NSUB = cpow(NS, DIM), NSF = cpow(NS, DIM - 1), HN = NS + 6, HSZ = cpow(HN, DIM);
     constexpr int NPOS = NSUB + 2 * DIM * NSF, NF3 = cpow(3, DIM - 1);
     constexpr int TRS = 2 * DIM * NV * NF3 * 3;   // trace size per position
-    constexpr int BIG = NSUB > NN ? NSUB : NN;
     constexpr int QF = cpow(3 * NS, DIM - 1);     // tangential quadrature points of one face
     constexpr int NFN = cpow(n, DIM - 1);
-    // sub-face fluxes (working precision), later the gather's intermediate stage
-    constexpr int FBB = DIM * (NS + 1) * NSF * NV * (int)sizeof(R), TMB = NV * BIG * 8;
+    // sub-face fluxes (working precision); the gather's intermediate stage and result later take
+    // their place
     R *Fb;
     double *tmp, *vn, *ug;
     if constexpr (BigCell<DIM, N>::on) {
@@ -1422,13 +1469,11 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
         vn = slot + BC::SUB_VN;
         ug = slot + BC::SUB_UG;
     } else {
-        // fbt: LDS of FBB > TMB ? FBB : TMB bytes (declared by the caller)
-        __shared__ double vn_[NV * BIG];
-        __shared__ double ug_[NV * BIG];
-        Fb = reinterpret_cast<R *>(fbt);
-        tmp = reinterpret_cast<double *>(fbt);
-        vn = vn_;
-        ug = ug_;
+        using LD = SubLds<DIM, N, R>;
+        Fb = reinterpret_cast<R *>(scr);
+        tmp = reinterpret_cast<double *>(scr);
+        ug = reinterpret_cast<double *>(scr + LD::UG);
+        vn = reinterpret_cast<double *>(scr + LD::VN);
     }
     __shared__ double red[2 * NV * (SUB_BS / 64)];
     __shared__ int badc;
@@ -1438,8 +1483,10 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
     coords_of(P, c, ci);
     const double dt = B.scal[0], t0 = B.scal[1];
     const R *tr = reinterpret_cast<const R *>(S.strace) + (int64_t)ch * NPOS * TRS;
+    using TRC = SubTrace<DIM, N>;
+    static_assert(TRC::SIZE <= (int64_t)NPOS * TRS, "the sub-face traces must fit the slot");
     const R gam = (R)P.gamma;
-    if (threadIdx.x == 0) badc = 0;
+    if (tid == 0) badc = 0;
     // neighbour existence per face of the cell: bit 2k + side; a face toward a solid cell
     // (masked geometry) has no neighbour and is a reflective wall (the same bit of nbwall)
     int nbex = 0, nbwall = 0;
@@ -1463,8 +1510,9 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
     // fallback by a ballot and the first of them sums the tangential points in order.
     constexpr int SPW = 64 / NF3;
     constexpr int PA = (NS + 1) * NSF, WPA = (PA + SPW - 1) / SPW;   // sub-faces, waves per axis
-    const int lane = threadIdx.x & 63, sfl = lane / NF3, ap = lane % NF3;
-    for (int wt = threadIdx.x >> 6; wt < DIM * WPA; wt += SUB_BS / 64) {
+    const int lane = tid & 63, sfl = lane / NF3, ap = lane % NF3;
+#pragma unroll 1
+    for (int wt = tid >> 6; wt < DIM * WPA; wt += SUB_BS / 64) {
         const int kk = wt / WPA;
         const int it2r = (wt % WPA) * SPW + sfl;
         const bool valid = sfl < SPW && it2r < PA;
@@ -1478,17 +1526,6 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
             // the first tangential axis takes sp % NS, the second sp / NS
             const int mp0 = sp % NS, mp1 = sp / NS;
             auto tang = [&](int j) -> int { return (j < k ? j : j - 1) == 0 ? mp0 : mp1; };
-            // positions left (f-1) and right (f) of the sub-face
-            auto pos_of = [&](int Lk) -> int {
-                if (Lk >= 0 && Lk < NS) {
-                    int idx = 0;
-#pragma unroll
-                    for (int j = DIM - 1; j >= 0; j--) idx = idx * NS + (j == k ? Lk : tang(j));
-                    return idx;
-                }
-                return NSUB + (2 * k + (Lk >= NS ? 1 : 0)) * NSF + sp;
-            };
-            const int pL = pos_of(f - 1), pR = pos_of(f);
             int low = 0;
             if constexpr (REDO) {
                 // flags of the subcells on both sides: own subcells, or the neighbour's layer
@@ -1546,12 +1583,11 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
                 for (int s = 0; s < 3; s++) {
                     R qL[NV], qR[NV], G[NV];
                     const double ts = t0 + T->xi3[s] * dt;
-                    const R *trL = tr + (int64_t)pL * TRS + (2 * k + 1) * NV * NF3 * 3;
-                    const R *trR = tr + (int64_t)pR * TRS + (2 * k + 0) * NV * NF3 * 3;
+                    const R *trk = tr + it2 * NF3 + ap;
 #pragma unroll
                     for (int v = 0; v < NV; v++) {
-                        qL[v] = pass ? (R)avL[v] : trL[v * NF3 * 3 + ap + NF3 * s];
-                        qR[v] = pass ? (R)avR[v] : trR[v * NF3 * 3 + ap + NF3 * s];
+                        qL[v] = pass ? (R)avL[v] : trk[TRC::at(k, 0, v, s)];
+                        qR[v] = pass ? (R)avR[v] : trk[TRC::at(k, 1, v, s)];
                     }
                     if (bside >= 0 && ((nbwall >> (2 * k + bside)) & 1)) {
                         // reflective wall of the masked geometry
@@ -1622,7 +1658,7 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
     __syncthreads();
     // FV update of the cell's own subcells
     const int slot = B.slot[1][c];
-    for (int sg = threadIdx.x; sg < NSUB; sg += SUB_BS) {
+    for (int sg = tid; sg < NSUB; sg += SUB_BS) {
         int ms[3] = {sg % NS, (sg / NS) % NS, sg / (NS * NS)};
         int hidx = 0;
         for (int j = DIM - 1; j >= 0; j--) hidx = hidx * HN + (ms[j] + 3);
@@ -1677,7 +1713,7 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
     if constexpr (BigCell<DIM, N>::on) {
         static_assert(FCT <= BigCell<DIM, N>::SUB_VN, "the stage must fit the sub-face flux region");
         __syncthreads();
-        for (int it = threadIdx.x; it < FCT; it += SUB_BS) {
+        for (int it = tid; it < FCT; it += SUB_BS) {
             const int a0 = it % n, q1 = (it / n) % QS, fv = it / (n * QS);   // fv = face * NV + v
             const double *fq = S.fpts + ((int64_t)ch * 2 * DIM * NV + fv) * QF + QS * q1;
             double acc = 0.0;
@@ -1685,7 +1721,7 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
             tmp[((int64_t)fv * n + a0) * QS + q1] = acc;
         }
         __syncthreads();
-        for (int it = threadIdx.x; it < 2 * DIM * NV * NFN; it += SUB_BS) {
+        for (int it = tid; it < 2 * DIM * NV * NFN; it += SUB_BS) {
             const int fv = it / NFN, a = it % NFN, a0 = a % n, a1 = a / n;
             const double *x = tmp + ((int64_t)fv * n + a0) * QS;
             double acc = 0.0;
@@ -1693,7 +1729,7 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
             B.sflux[(int64_t)slot * 2 * DIM * NV * NFN + it] = acc;
         }
     } else {
-        for (int it = threadIdx.x; it < 2 * DIM * NV * NFN; it += SUB_BS) {
+        for (int it = tid; it < 2 * DIM * NV * NFN; it += SUB_BS) {
             const int face = it / (NV * NFN), v = (it / NFN) % NV, a = it % NFN;
             const int a0 = a % n, a1 = a / n;
             const double *fq = S.fpts + ((int64_t)ch * 2 * DIM + face) * NV * QF + v * QF;
@@ -1711,228 +1747,267 @@ __device__ __forceinline__ void sub_update_cell(const Tables *__restrict__ T, co
         }
     }
     __syncthreads();
-    store_cell_bounds<NV>(P, B, c, vn, NSUB, threadIdx.x, SUB_BS, red);
+    store_cell_bounds<NV>(P, B, c, vn, NSUB, tid, SUB_BS, red);
     // gather: u = R v (eq. (subcell.r)), tensor application
-    tensor_apply<DIM, n, NS, NV, MAXNS>(&T->Rg[0][0], vn, ug, tmp, threadIdx.x, SUB_BS);
-    for (int it = threadIdx.x; it < NV * NN; it += SUB_BS) {
+    tensor_apply<DIM, n, NS, NV, MAXNS>(&T->Rg[0][0], vn, ug, tmp, tid, SUB_BS);
+    for (int it = tid; it < NV * NN; it += SUB_BS) {
         const int v = it / NN, a = it % NN;
         B.u[cur ^ 1][((int64_t)v * P.ncell + c) * NN + a] = ug[it];
     }
-    if (threadIdx.x == 0 && badc) atomicAdd(nonphys, 1);
+    if (tid == 0 && badc) atomicAdd(nonphys, 1);
     __syncthreads();   // LDS reused by the next troubled cell
 }
 
 // S3: degree-2 local space-time predictor (eq. (pde.nc.dg2) on the subgrid, mesh size
-// h/Ns, three sweeps) of every position of one troubled cell.  The 3^d spatial nodes of a
-// position sit on consecutive lanes of one wave (64 / 3^d positions per wave), each lane
-// holding its node's time pencil; a contraction along an axis gathers the three nodes of
-// the line by lane permutation, so the waves work without LDS or workgroup barriers.
-// Output: the face traces of every position, [pos][2d][v][3^(d-1) tangential x 3 time],
-// in the working precision R (FP32 in the mixed form).
-template <int DIM, typename R, bool XCH = false>
-__device__ void sub_predictor(const Tables *__restrict__ T, const R *__restrict__ Y, R *__restrict__ tr,
-                              int npos, int nsub, int nsf, double dt, const double *dth, double gamma_d,
-                              R *xch = nullptr) {
-    constexpr int NV = DIM + 2, NN = cpow(3, DIM), NF = cpow(3, DIM - 1), PPW = 64 / NN;
-    constexpr int TRS = 2 * DIM * NV * NF * 3;
-    constexpr int ST[3] = {1, 3, 9};
+// h/Ns, three sweeps) of every position of one troubled cell.  A lane holds the three nodes of
+// one line along x with their time pencils, so 3^(d-1) consecutive lanes make a position (21
+// positions per wave in 2D, 7 in 3D).  The contraction along x runs in registers; along the
+// other axes a lane writes its line's fluxes to its LDS row and reads those of the two other
+// lines (its wave's rows only: no workgroup barrier).  The time slices are taken one after the
+// other, each divergence replacing its slice, so that a lane holds three slices and the
+// divergence in progress.
+// Output: the face traces in SubTrace's order, in the working precision R (FP32 in the mixed
+// form).
+// Bound by vector issue and by the latency of the exchange at two to three waves per SIMD.
+// Measured per troubled cell and workgroup against one lane per node (54 of 64 lanes busy in 3D,
+// every axis exchanged): 3D N = 3 419 -> 227 us (FP32), 805 -> 468 us (FP64); 2D N = 5
+// 42 -> 22 us (FP64, with N = 4). The loops over positions and sweeps are not unrolled: unrolled,
+// their live values spilled (2D FP64 42 -> 101 us).
+template <int DIM, int N, typename R>
+__device__ __forceinline__ void sub_predictor(TabC T, const R *__restrict__ Y, R *__restrict__ tr,
+                                              double dt, const double *dth, double gamma_d, R *rows, int tid) {
+    using TRC = SubTrace<DIM, N>;
+    constexpr int NV = DIM + 2, NN = cpow(3, DIM), NL = cpow(3, DIM - 1), PPW = 64 / NL;
+    constexpr int NS = 2 * N + 1, NSUB = cpow(NS, DIM), NSF = cpow(NS, DIM - 1), NPOS = NSUB + 2 * DIM * NSF;
     constexpr bool F32 = sizeof(R) == 4;
+    constexpr int NVAL = SubRow<DIM, R>::NVAL, RS = SubRow<DIM, R>::STRIDE;
     const R gamma = (R)gamma_d;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int slot = lane / NN, a = lane % NN;
-    const int ia[3] = {a % 3, (a / 3) % 3, a / 9};
-    // Along each axis a lane needs the values of the two other nodes of its line: it reads
-    // them from the lanes of line nodes (ia + 1) % 3 and (ia + 2) % 3 (two lane permutations
-    // per value; its own node's value it has).  Dk[k][j]: this lane's derivative-matrix row
-    // in that order (own node first); src1/src2: the two source lanes.
-    R Dk[DIM][3], ck[DIM];
-    int src1[DIM], src2[DIM];
+    const int lane = tid & 63, wv = tid >> 6;
+    const int slot = lane / NL, line = lane % NL;
+    // node index of the line along y (and z)
+    const int ja[2] = {line % 3, line / 3};
+    R *wrow = rows + (int64_t)wv * 64 * RS;
+    R *own = wrow + lane * RS;
+    // along axis 1 + j: the rows of line nodes (ja + 1) % 3 and (ja + 2) % 3, and this lane's row of
+    // (dt Ns / h) D in that order (own node first); lanes beyond the last position read their own
+    // row
+    const R *nb1[DIM - 1], *nb2[DIM - 1];
+    R Dk[DIM - 1][3];
+    const R cx = (R)(dt * dth[0]);
 #pragma unroll
-    for (int k = 0; k < DIM; k++) {
-        ck[k] = (R)(dt * dth[k]);
-        const int r = ia[k], n1 = (r + 1) % 3, n2 = (r + 2) % 3;
-        Dk[k][0] = F32 ? (R)T->fD3[r][r] : (R)T->D3[r][r];
-        Dk[k][1] = F32 ? (R)T->fD3[r][n1] : (R)T->D3[r][n1];
-        Dk[k][2] = F32 ? (R)T->fD3[r][n2] : (R)T->D3[r][n2];
-        src1[k] = lane + (n1 - r) * ST[k];
-        src2[k] = lane + (n2 - r) * ST[k];
+    for (int j = 0; j < DIM - 1; j++) {
+        const int st = j == 0 ? 1 : 3, r = ja[j], n1 = (r + 1) % 3, n2 = (r + 2) % 3;
+        const R ck = (R)(dt * dth[1 + j]);
+        Dk[j][0] = ck * (F32 ? (R)T->fD3[r][r] : (R)T->D3[r][r]);
+        Dk[j][1] = ck * (F32 ? (R)T->fD3[r][n1] : (R)T->D3[r][n1]);
+        Dk[j][2] = ck * (F32 ? (R)T->fD3[r][n2] : (R)T->D3[r][n2]);
+        nb1[j] = own + (slot < PPW ? (n1 - r) * st * RS : 0);
+        nb2[j] = own + (slot < PPW ? (n2 - r) * st * RS : 0);
     }
-    for (int base = wv * PPW; base < npos; base += nw * PPW) {
-        const int pos = base + slot;
-        const bool valid = slot < PPW && pos < npos;
-        R u0[NV], q[NV][3];
-        if (valid) {
+    // orders a wave's row accesses (lanes of one wave only)
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    typedef R Vec __attribute__((ext_vector_type(16 / sizeof(R))));
+    constexpr int VL = 16 / (int)sizeof(R), NVEC = (NVAL + VL - 1) / VL;
+    auto put_row = [&](const R(&x)[NVEC * VL]) {
 #pragma unroll
-            for (int v = 0; v < NV; v++) u0[v] = (R)Y[((int64_t)pos * NV + v) * NN + a];
-        } else {
-            // idle lanes carry a valid constant state
+        for (int i = 0; i < NVEC; i++) {
+            Vec w;
 #pragma unroll
-            for (int v = 0; v < NV; v++) u0[v] = (v == 0) ? R(1) : R(0);
-            u0[NV - 1] = R(2.5);
+            for (int e = 0; e < VL; e++) w[e] = x[i * VL + e];
+            *reinterpret_cast<Vec *>(own + i * VL) = w;
         }
+    };
+    // S += sum_k (dt Ns / h_k) D_k F_k(q) at one time slice, q and S as [v][x node]
+    auto divergence = [&](const R(&q)[NV][3], R(&S)[NV][3]) {
+        R vel[DIM][3], p[3];
 #pragma unroll
-        for (int v = 0; v < NV; v++)
+        for (int i = 0; i < 3; i++) {
+            const R ir = recip(q[0][i]);
+            R ke = 0;
 #pragma unroll
-            for (int s = 0; s < 3; s++) q[v][s] = u0[v];
-        // Three Picard sweeps.  The first starts from u^n at every time node, so its fluxes and
-        // their derivatives are the same on the three time slices: slice 0 is computed and
-        // copied (nt: time slices computed, uniform over the wave).
-        for (int r = 0; r < 3; r++) {
-            const int nt = r == 0 ? 1 : 3;
-            R S[NV][3];
+            for (int j = 0; j < DIM; j++) {
+                vel[j][i] = q[1 + j][i] * ir;
+                ke += q[1 + j][i] * vel[j][i];
+            }
+            p[i] = (gamma - R(1)) * (q[NV - 1][i] - R(0.5) * ke);
+        }
+        auto flux = [&](int k, int v, int i) -> R {
+            if (v == 0) return q[1 + k][i];
+            if (v == NV - 1) return vel[k][i] * (q[NV - 1][i] + p[i]);
+            return q[v][i] * vel[k][i] + (v == 1 + k ? p[i] : R(0));
+        };
+        // along x in registers
 #pragma unroll
-            for (int k = 0; k < DIM; k++) {
-                R F[NV][3];
+        for (int v = 0; v < NV; v++) {
+            R F[3];
 #pragma unroll
-                for (int t = 0; t < 3; t++) {
-                    if (t >= nt) break;
-                    const R ir = recip(q[0][t]);
-                    const R un = q[1 + k][t] * ir;
-                    R ke = 0;
+            for (int i = 0; i < 3; i++) F[i] = cx * flux(0, v, i);
 #pragma unroll
-                    for (int j = 0; j < DIM; j++) ke += q[1 + j][t] * q[1 + j][t];
-                    const R prt = (gamma - R(1)) * (q[NV - 1][t] - R(0.5) * ke * ir);
-                    F[0][t] = q[1 + k][t];
+            for (int i = 0; i < 3; i++) {
+                R acc = 0;
 #pragma unroll
-                    for (int j = 0; j < DIM; j++) F[1 + j][t] = q[1 + j][t] * un + (j == k ? prt : R(0));
-                    F[NV - 1][t] = un * (q[NV - 1][t] + prt);
+                for (int b = 0; b < 3; b++) acc += (F32 ? (R)T->fD3[i][b] : (R)T->D3[i][b]) * F[b];
+                S[v][i] = acc;
+            }
+        }
+        // along y (and z) through the rows
+#pragma unroll
+        for (int j = 0; j < DIM - 1; j++) {
+            R F[NVEC * VL];
+#pragma unroll
+            for (int e = NVAL; e < NVEC * VL; e++) F[e] = 0;
+#pragma unroll
+            for (int v = 0; v < NV; v++)
+#pragma unroll
+                for (int i = 0; i < 3; i++) {
+                    F[v * 3 + i] = flux(1 + j, v, i);
+                    S[v][i] += Dk[j][0] * F[v * 3 + i];
                 }
-                // sum_b D[a_k][b] F(node b of the line): own node, then (ia + 1) % 3, (ia + 2) % 3
-                // all lane permutations of the axis first (independent, in flight together); with an
-                // exchange buffer (3D), through the wave's own LDS rows instead: each lane writes its
-                // fluxes once and reads those of its two line neighbours
-                R g1[NV][3], g2[NV][3], x[NV][3];
-                if constexpr (XCH) {
-                    R *xw = xch + (int64_t)wv * 64 * NV * 3;
+            put_row(F);
+            wave_sync();
 #pragma unroll
-                    for (int v = 0; v < NV; v++)
+            for (int c = 0; c < NVEC; c++) {
+                const Vec g1 = *reinterpret_cast<const Vec *>(nb1[j] + c * VL);
+                const Vec g2 = *reinterpret_cast<const Vec *>(nb2[j] + c * VL);
 #pragma unroll
-                        for (int t = 0; t < 3; t++)
-                            if (t < nt) xw[lane * (NV * 3) + v * 3 + t] = F[v][t];
-                    // lanes of one wave only: order the writes before the reads at wave scope
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                    for (int v = 0; v < NV; v++)
-#pragma unroll
-                        for (int t = 0; t < 3; t++)
-                            if (t < nt) {
-                                // (source lanes taken mod 64 as a lane permutation takes them: the
-                                // idle lanes past the last position stay within the wave's rows)
-                                g1[v][t] = xw[(src1[k] & 63) * (NV * 3) + v * 3 + t];
-                                g2[v][t] = xw[(src2[k] & 63) * (NV * 3) + v * 3 + t];
-                            }
-                    // the next axis overwrites the rows only after every lane has read them
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 3; t++) {
-                        if (t >= nt) break;
-#pragma unroll
-                        for (int v = 0; v < NV; v++) {
-                            g1[v][t] = __shfl(F[v][t], src1[k]);
-                            g2[v][t] = __shfl(F[v][t], src2[k]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int t = 0; t < 3; t++) {
-                    if (t >= nt) break;
-#pragma unroll
-                    for (int v = 0; v < NV; v++) {
-                        x[v][t] = Dk[k][0] * F[v][t] + Dk[k][1] * g1[v][t] + Dk[k][2] * g2[v][t];
-                        S[v][t] = (k == 0) ? ck[k] * x[v][t] : S[v][t] + ck[k] * x[v][t];
-                    }
+                for (int e = 0; e < VL; e++) {
+                    const int at = c * VL + e;
+                    if (at < NVAL) S[at / 3][at % 3] += Dk[j][1] * g1[e] + Dk[j][2] * g2[e];
                 }
             }
-            if (nt == 1) {
+            wave_sync();   // the rows are overwritten only after every lane has read them
+        }
+    };
+#pragma unroll 1
+    for (int base = wv * PPW; base < NPOS; base += (SUB_BS / 64) * PPW) {
+        const bool valid = slot < PPW && base + slot < NPOS;
+        const int pos = valid ? base + slot : NPOS - 1;   // idle lanes repeat the last position
+        const R *y = Y + (int64_t)pos * NV * NN + line * 3;
+        R q[3][NV][3];   // [time node][v][x node]
+        {
+            // first sweep: u^n at every time node, so one slice stands for all of them
+            R u0[NV][3], S[NV][3];
 #pragma unroll
-                for (int v = 0; v < NV; v++) S[v][1] = S[v][2] = S[v][0];
-            }
-            // time contraction K1^{-1} diag(w)
+            for (int v = 0; v < NV; v++)
+#pragma unroll
+                for (int i = 0; i < 3; i++) u0[v][i] = y[v * NN + i];
+            divergence(u0, S);
 #pragma unroll
             for (int s = 0; s < 3; s++) {
-                R acc[NV];
+                const R ks = F32 ? (R)T->fKw3[s][0] + (R)T->fKw3[s][1] + (R)T->fKw3[s][2]
+                                 : (R)T->Kw3[s][0] + (R)T->Kw3[s][1] + (R)T->Kw3[s][2];
 #pragma unroll
-                for (int v = 0; v < NV; v++) acc[v] = 0;
+                for (int v = 0; v < NV; v++)
 #pragma unroll
-                for (int t = 0; t < 3; t++) {
-                    const R kst = F32 ? (R)T->fKw3[s][t] : (R)T->Kw3[s][t];
-#pragma unroll
-                    for (int v = 0; v < NV; v++) acc[v] += kst * S[v][t];
-                }
-#pragma unroll
-                for (int v = 0; v < NV; v++) q[v][s] = u0[v] - acc[v];
+                    for (int i = 0; i < 3; i++) q[s][v][i] = u0[v][i] - ks * S[v][i];
             }
         }
-        // face traces: the lane at the low end of a line writes the xi_k = 0 trace, the lane
-        // at the high end the xi_k = 1 trace (with the exchange buffer, the pencils are written
-        // once for the three axes)
-        R *xq = xch + (int64_t)wv * 64 * NV * 3;
-        if constexpr (XCH) {
+#pragma unroll 1
+        for (int r = 1; r < 3; r++) {
+            // q^{r+1}(s) = u0 - sum_t Kw[s][t] S(t), the divergences S(t) in the place of the slices
+            // they were taken from
+#pragma unroll
+            for (int t = 0; t < 3; t++) {
+                R S[NV][3];
+                divergence(q[t], S);
+#pragma unroll
+                for (int v = 0; v < NV; v++)
+#pragma unroll
+                    for (int i = 0; i < 3; i++) q[t][v][i] = S[v][i];
+            }
 #pragma unroll
             for (int v = 0; v < NV; v++)
 #pragma unroll
-                for (int s = 0; s < 3; s++) xq[lane * (NV * 3) + v * 3 + s] = q[v][s];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+                for (int i = 0; i < 3; i++) {
+                    const R S0 = q[0][v][i], S1 = q[1][v][i], S2 = q[2][v][i], u0 = y[v * NN + i];
 #pragma unroll
-        for (int k = 0; k < DIM; k++) {
-            // the line's three nodes in this lane's order: own, (ia + 1) % 3, (ia + 2) % 3
-            R qb[3][NV][3];
-#pragma unroll
-            for (int v = 0; v < NV; v++)
-#pragma unroll
-                for (int s = 0; s < 3; s++) {
-                    qb[0][v][s] = q[v][s];
-                    if constexpr (XCH) {
-                        qb[1][v][s] = xq[(src1[k] & 63) * (NV * 3) + v * 3 + s];
-                        qb[2][v][s] = xq[(src2[k] & 63) * (NV * 3) + v * 3 + s];
-                    } else {
-                        qb[1][v][s] = __shfl(q[v][s], src1[k]);
-                        qb[2][v][s] = __shfl(q[v][s], src2[k]);
+                    for (int s = 0; s < 3; s++) {
+                        const R k0 = F32 ? (R)T->fKw3[s][0] : (R)T->Kw3[s][0];
+                        const R k1 = F32 ? (R)T->fKw3[s][1] : (R)T->Kw3[s][1];
+                        const R k2 = F32 ? (R)T->fKw3[s][2] : (R)T->Kw3[s][2];
+                        R acc = k0 * S0;
+                        acc += k1 * S1;
+                        acc += k2 * S2;
+                        q[s][v][i] = u0 - acc;
                     }
                 }
-            // a neighbour-layer position (pos >= nsub) only needs the trace on its face toward
-            // the cell: the + face of the low layer, the - face of the high layer
-            const int layer = pos >= nsub ? (pos - nsub) / nsf : -1;
-            const bool needed = layer < 0 || ((layer >> 1) == k && (layer & 1) == (ia[k] == 0));
-            if (valid && ia[k] != 1 && needed) {
-                const int side = ia[k] == 2;
-                const int r = ia[k], nb[3] = {r, (r + 1) % 3, (r + 2) % 3};
-                R Bv[3];
+        }
+        // Face traces.  The position's own subcells serve the sub-faces on both their sides; a
+        // position of the neighbour layer only the one toward the cell (the + face of the low
+        // layer, the - face of the high layer).
+        int L[3];
+        position_coords<DIM>(pos, NS, L);
+        const int layer = pos >= NSUB ? (pos - NSUB) / NSF : -1;
+        auto subface = [&](int k, int side) -> int {
+            int sp = 0, mul = 1;
 #pragma unroll
-                for (int b = 0; b < 3; b++)
-                    Bv[b] = F32 ? (R)(side ? T->fR3[nb[b]] : T->fL3[nb[b]]) : (R)(side ? T->R3[nb[b]] : T->L3[nb[b]]);
-                int ap = 0, mul = 1;
+            for (int j = 0; j < DIM; j++) {
+                if (j == k) continue;
+                sp += L[j] * mul;
+                mul *= NS;
+            }
+            const int Lk = k == 0 ? L[0] : (k == 1 ? L[1] : L[2]);
+            return (Lk + side) * NSF + sp;
+        };
+        auto wanted = [&](int k, int side) { return valid && (layer < 0 || layer == 2 * k + 1 - side); };
+        auto end_row = [&](int side, int b) -> R {
+            return F32 ? (R)(side ? T->fR3[b] : T->fL3[b]) : (R)(side ? T->R3[b] : T->L3[b]);
+        };
 #pragma unroll
-                for (int j = 0; j < DIM; j++) {
-                    if (j == k) continue;
-                    ap += ia[j] * mul;
-                    mul *= 3;
-                }
-                R *o = tr + (int64_t)pos * TRS + (2 * k + side) * NV * NF * 3;
+        for (int side = 0; side < 2; side++)
+            if (wanted(0, side)) {
+                R *o = tr + subface(0, side) * NL + line;
 #pragma unroll
                 for (int v = 0; v < NV; v++)
 #pragma unroll
                     for (int s = 0; s < 3; s++) {
                         R acc = 0;
 #pragma unroll
-                        for (int b = 0; b < 3; b++) acc += Bv[b] * qb[b][v][s];
-                        o[v * NF * 3 + ap + NF * s] = acc;
+                        for (int b = 0; b < 3; b++) acc += end_row(side, b) * q[s][v][b];
+                        o[TRC::at(0, 1 - side, v, s)] = acc;
                     }
             }
-        }
-        if constexpr (XCH) {
-            // the next positions' sweep overwrites the rows only after every lane has read them
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // along y (and z) the three lanes of a line share out its x nodes: lane ja takes x node ja
+#pragma unroll
+        for (int s = 0; s < 3; s++) {
+            R x[NVEC * VL];
+#pragma unroll
+            for (int e = NVAL; e < NVEC * VL; e++) x[e] = 0;
+#pragma unroll
+            for (int v = 0; v < NV; v++)
+#pragma unroll
+                for (int i = 0; i < 3; i++) x[v * 3 + i] = q[s][v][i];
+            put_row(x);
+            wave_sync();
+#pragma unroll
+            for (int j = 0; j < DIM - 1; j++) {
+                const int st = j == 0 ? 1 : 3;
+                const R *r0 = own - (slot < PPW ? ja[j] * st * RS : 0);
+                const int step = slot < PPW ? st * RS : 0;
+                R xb[NV][3];
+#pragma unroll
+                for (int v = 0; v < NV; v++)
+#pragma unroll
+                    for (int b = 0; b < 3; b++) xb[v][b] = r0[b * step + v * 3 + ja[j]];
+                const int ap = DIM == 3 ? ja[j] + 3 * ja[1 - j] : ja[j];
+#pragma unroll
+                for (int side = 0; side < 2; side++)
+                    if (wanted(1 + j, side)) {
+                        R *o = tr + subface(1 + j, side) * NL + ap;
+#pragma unroll
+                        for (int v = 0; v < NV; v++) {
+                            R acc = 0;
+#pragma unroll
+                            for (int b = 0; b < 3; b++) acc += end_row(side, b) * xb[v][b];
+                            o[TRC::at(1 + j, 1 - side, v, s)] = acc;
+                        }
+                    }
+            }
+            wave_sync();
         }
     }
 }
@@ -1950,6 +2025,10 @@ __device__ void sub_predictor(const Tables *__restrict__ T, const R *__restrict_
 template <int DIM, int N, typename R, bool REDO>
 __device__ __forceinline__ void subcell_cell(const Tables *__restrict__ T, const Prob &P, const Bufs &B, int cur,
                                              int w, int sidx, const SubScratch &S, int *nonphys, int flagging) {
+    // the thread index made opaque: otherwise the phases' index arithmetic, the same for every
+    // troubled cell, is hoisted out of the loop over the cells and spilled
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
     constexpr int NV = DIM + 2, NS = 2 * N + 1, NSUB = cpow(NS, DIM), NSF = cpow(NS, DIM - 1);
     constexpr int NPOS = NSUB + 2 * DIM * NSF, N3 = cpow(3, DIM);
     constexpr int TRS = 2 * DIM * NV * cpow(3, DIM - 1) * 3;
@@ -1958,33 +2037,25 @@ __device__ __forceinline__ void subcell_cell(const Tables *__restrict__ T, const
     for (int k = 0; k < DIM; k++) dth[k] = (double)NS / P.h[k];
     const R *Ys = reinterpret_cast<const R *>(S.Y) + (int64_t)sidx * NPOS * NV * N3;
     R *trs = reinterpret_cast<R *>(S.strace) + (int64_t)sidx * NPOS * TRS;
-    // 2D: the halo and the source cells' coefficients live in LDS; 3D: halo in HBM scratch
-    constexpr int HSZ = cpow(NS + 6, DIM), NNS = cpow(N + 1, DIM);
+    // 2D: the halo lives in LDS; 3D: in the slot
+    constexpr int HSZ = cpow(NS + 6, DIM);
     __shared__ double halo_s[DIM == 2 ? NV * HSZ : 1];
-    // 2D: the source cells' coefficients of the halo, later the predictor's line-exchange rows
-    constexpr int XROWS = (SUB_BS / 64) * 64 * NV * 3 * (int)sizeof(R) / 8;   // doubles
-    __shared__ double nbu_s[DIM == 2 ? (9 * NV * NNS > XROWS ? 9 * NV * NNS : XROWS) : 1];
     __shared__ double mb[2][NV];      // m_i, M_i of eq. (dmp) (MOOD flags)
     __shared__ int nslot[3][2];       // pool slots of troubled face neighbours (MOOD recompute)
     double *halo = (DIM == 2) ? halo_s : S.halo + (int64_t)sidx * NV * HSZ;
-    double *nbu = (DIM == 2) ? nbu_s : nullptr;
-    // LDS of the update's sub-face fluxes and of the gather's intermediate stage (large cells:
-    // their global slot); in 3D the halo's sum-factorisation stages use it first
-    constexpr int n = N + 1, NN = cpow(n, DIM), BIGN = NSUB > NN ? NSUB : NN;
-    constexpr int FBB = DIM * (NS + 1) * NSF * NV * (int)sizeof(R), TMB = NV * BIGN * 8;
-    constexpr int FBT = FBB > TMB ? FBB : TMB;
-    __shared__ __align__(16) unsigned char fbt[BigCell<DIM, N>::on ? 16 : FBT];
-    static_assert(DIM == 2 || BigCell<DIM, N>::on || (NV * NS * n * n + NV * NS * NS * n) * 8 <= FBT,
-                  "the 3D halo's stage buffers must fit the sub-face flux LDS");
-    static_assert(!BigCell<DIM, N>::on || NV * NS * n * n + NV * NS * NS * n <= BigCell<DIM, N>::SUB_VN,
+    // one LDS block for what the phases hold one after the other
+    using LD = SubLds<DIM, N, R>;
+    __shared__ __align__(16) unsigned char scr[LD::BYTES];
+    double *nbu = (DIM == 2) ? reinterpret_cast<double *>(scr) : nullptr;
+    static_assert(!BigCell<DIM, N>::on || NV * NS * (N + 1) * (N + 1) + NV * NS * NS * (N + 1) <= BigCell<DIM, N>::SUB_VN,
                   "the 3D halo's stage buffers must fit the slot's sub-face flux region");
-    double *hst = BigCell<DIM, N>::on ? S.big + (int64_t)sidx * BigCell<DIM, N>::SLOT : reinterpret_cast<double *>(fbt);
+    double *hst = BigCell<DIM, N>::on ? S.big + (int64_t)sidx * BigCell<DIM, N>::SLOT : reinterpret_cast<double *>(scr);
     {
         const int64_t c = B.tlist[w];
         if (!REDO && flagging) {
             // neighbourhood bounds of the cell, as in the detection
-            if (threadIdx.x < 2 * NV) {
-                const int mm = threadIdx.x / NV, v = threadIdx.x % NV;
+            if (tid < 2 * NV) {
+                const int mm = tid / NV, v = tid % NV;
                 int ci[3];
                 coords_of(P, c, ci);
                 int ne[3] = {1, 1, 1};
@@ -2008,8 +2079,8 @@ __device__ __forceinline__ void subcell_cell(const Tables *__restrict__ T, const
         }
         if constexpr (REDO) {
             // neighbour slots, then: does a flagged subcell touch one of this cell's sub-faces?
-            if (threadIdx.x < 2 * DIM) {
-                const int k = threadIdx.x >> 1, side = threadIdx.x & 1;
+            if (tid < 2 * DIM) {
+                const int k = tid >> 1, side = tid & 1;
                 int ci[3];
                 coords_of(P, c, ci);
                 // the neighbour's coordinate along k, then its cell (selections, no dynamic index)
@@ -2031,7 +2102,7 @@ __device__ __forceinline__ void subcell_cell(const Tables *__restrict__ T, const
             __syncthreads();
             const int own = B.slot[1][c];
             int any = 0;
-            for (int i = threadIdx.x; i < NSUB + 2 * DIM * NSF; i += SUB_BS) {
+            for (int i = tid; i < NSUB + 2 * DIM * NSF; i += SUB_BS) {
                 if (i < NSUB) {
                     any |= B.mflag[(int64_t)own * NSUB + i];
                 } else {
@@ -2050,20 +2121,23 @@ __device__ __forceinline__ void subcell_cell(const Tables *__restrict__ T, const
                 }
             }
             if (!__syncthreads_or(any)) return;
-            if (threadIdx.x == 0) atomicAdd(&B.counts[6], 1);
+            if (tid == 0) atomicAdd(&B.counts[6], 1);
         }
-        if constexpr (DIM == 3) sub_halo_cell3<N>(T, P, B, cur, w, halo, hst);
-        else sub_halo_cell<DIM, N>(T, P, B, cur, w, halo, nbu);
+        // every phase reads the tables through a pointer of its own, made opaque: scalar loads where
+        // they are used, instead of one set of registers held (and spilled) across all phases
+        auto tab = [&]() -> TabC {
+            TabC t = (TabC)T;
+            __asm__ volatile("" : "+s"(t));
+            return t;
+        };
+        if constexpr (DIM == 3) sub_halo_cell3<N>(tab(), P, B, cur, w, halo, hst, tid);
+        else sub_halo_cell<DIM, N>(tab(), P, B, cur, w, halo, nbu, tid);
         __syncthreads();
-        sub_recon_cell<DIM, N, R>(T, S.Y, sidx, halo, trs);
+        sub_recon_cell<DIM, N, R>(tab(), S.Y, sidx, halo, trs, tid);
         __syncthreads();
-        // the line exchange of the predictor through LDS rows (free in this phase): in 2D the halo's
-        // staging LDS, in 3D the flux LDS where the rows fit (not for large cells)
-        constexpr bool XCH = DIM == 2 || (!BigCell<DIM, N>::on && (SUB_BS / 64) * 64 * NV * 3 * (int)sizeof(R) <= FBT);
-        R *xrows = DIM == 2 ? reinterpret_cast<R *>(nbu_s) : reinterpret_cast<R *>(fbt);
-        sub_predictor<DIM, R, XCH>(T, Ys, trs, NPOS, NSUB, NSF, dt, dth, P.gamma, xrows);
+        sub_predictor<DIM, N, R>(tab(), Ys, trs, dt, dth, P.gamma, reinterpret_cast<R *>(scr), tid);
         __syncthreads();
-        sub_update_cell<DIM, N, R, REDO>(T, P, B, cur, w, sidx, S, nonphys, halo, REDO ? 0 : flagging, mb, nslot, fbt);
+        sub_update_cell<DIM, N, R, REDO>(tab(), P, B, cur, w, sidx, S, nonphys, halo, REDO ? 0 : flagging, mb, nslot, scr, tid);
     }
 }
 
