@@ -15,6 +15,15 @@ namespace adg {
 // and stores them in LDS; "line owner" threads do the length-n spatial contractions
 // (n loads -> n outputs each, in place); the point owner accumulates S over the d axes
 // and applies the time contraction in registers: d + 1 contractions per sweep.
+// What bounds it: vector instructions, the matrix unit and LDS take about a third of the time each
+// (2D N = 9, FP32: 36 %, 34 %, 42 %), one after the other between the barriers of a workgroup, with
+// four waves per SIMD to overlap them.  So FP32 has its contractions on the matrix unit, 8-byte LDS
+// accesses without bank conflicts (33 % of the LDS time before) and no barrier between a point's
+// last read and its owner's next store; traces and volume term take one line / node per thread.
+// Measured against contractions on the vector unit, 4-byte accesses and items spread over the
+// threads (FP32): 2D N = 5, 400 x 100 cells 246 -> 192 us; N = 4, 131 x 75 41.9 -> 31.2 us; N = 3,
+// 48 problems 474 -> 302 us; N = 9, 64 x 64 240 -> 232 us; 3D N = 3, 128^3 17.9 -> 12.7 ms.  FP64
+// (traces, volume term and barriers only): 3D N = 3, 64^3 4.63 -> 4.05 ms.
 template <int DIM, int N, typename R = double, int TB = Tune<DIM, N, sizeof(R) == 4>::pred_tb>
 struct PredShape;
 
@@ -22,6 +31,14 @@ struct PredShape;
 // the FP32 working precision of the mixed form.
 __device__ __forceinline__ double recip(double x) { return 1.0 / x; }
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
+
+// x / d with ir = recip(d): the division itself in FP64; in FP32 the product corrected by its
+// residual, which rounds like the division.
+__device__ __forceinline__ double quotient(double x, double d, double) { return x / d; }
+__device__ __forceinline__ float quotient(float x, float d, float ir) {
+    const float y = x * ir;
+    return fmaf(fmaf(-y, d, x), ir, y);
+}
 
 // TB: thread budget of a workgroup (cells per block = TB / n^d)
 template <int DIM, int N, typename R, int TB>
@@ -38,15 +55,218 @@ struct PredShape {
     static constexpr int VC = VCMAX < 1 ? 1 : (VCMAX > NV ? NV : VCMAX);  // vars per LDS chunk
 };
 
+// ---- FP32 contractions on the matrix unit (4x4x1, 16 blocks).  Lane l of a wave is column l % 4
+// of block l / 4: its B operand is one value of the pencil or line it owns and the four
+// registers of the accumulator are four consecutive outputs of that line, so a lane's data stay
+// in its own registers.  The A operand is broadcast from one block (lane group) to all sixteen:
+// block b of one register holds column b of four operator rows, so a whole operator of n <= 10
+// nodes takes one register per four rows and no operand is read in the loops.
+typedef float mvec __attribute__((ext_vector_type(4)));
+template <int B>
+__device__ __forceinline__ mvec mat4(float a, float x, mvec acc) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, x, acc, 4, B, 0);
+}
+// acc[g] += (rows 4g .. 4g + 3, columns B .. B + C - 1 of the operator in a) x[0 .. C - 1]
+template <int B, int C, int G>
+__device__ __forceinline__ void mat_cols(const float *a, const float *x, mvec *acc) {
+    if constexpr (C > 0) {
+#pragma unroll
+        for (int g = 0; g < G; g++) acc[g] = mat4<B>(a[g], x[0], acc[g]);
+        mat_cols<B + 1, C - 1, G>(a, x + 1, acc);
+    }
+}
+template <int N>
+struct MatOps {
+    static constexpr int n = N + 1, h = n / 2, hu = n - h;
+    static constexpr bool EO = n >= 6;          // even / odd form of the derivative
+    static constexpr int G = (n + 3) / 4;       // row groups of an n x n operator
+    static constexpr int GE = (h + 3) / 4, GO = (hu + 3) / 4, GD = EO ? GO : G;
+    static constexpr int OB = 8;                // first block of the odd part (columns of the even part: hu <= 5)
+    float kw[G];                                // time operator
+    float d[GD];                                // derivative: E in blocks 0 .., O in blocks OB ..
+};
+// Layout of the predictor's LDS array: every cell holds VC variables at n^d nodes and n time
+// levels.  FP64 and n < 4: one plane per variable.  Matrix-unit form: variables in pairs (8-byte
+// accesses; a last odd variable alone) and an odd number of nodes per time level, so that with
+// the line order of LineMap the 16 lanes of an 8-byte access start in 16 different bank pairs.
+template <int DIM, int N, int VC, typename R>
+struct PredLds {
+    static constexpr int n = N + 1;
+    static constexpr bool MAT = sizeof(R) == 4 && n >= 4;
+    static constexpr int SS = MAT ? cpow(n, DIM) | 1 : cpow(n, DIM);   // time level
+    static constexpr int PTS = SS * n;                        // points of one variable
+    static constexpr int CELL = MAT ? (VC * PTS + 1) / 2 * 2 : VC * PTS;
+    static constexpr bool paired(int v) { return MAT && (v | 1) < VC; }
+    static constexpr int at(int v) { return paired(v) ? v / 2 * 2 * PTS + (v & 1) : v * PTS; }
+    static constexpr int es(int v) { return paired(v) ? 2 : 1; }
+    static constexpr int stride(int k) { return k == 0 ? 1 : (k == 1 ? n : n * n); }   // along axis k
+    // first point of line j = a_perp + n^(d-1) s along axis k
+    static constexpr int line(int k, int j) {
+        const int nf = cpow(n, DIM - 1), st = stride(k), ap = j % nf;
+        return SS * (j / nf) + ap % st + ap / st * st * n;
+    }
+};
+// The line that thread i contracts along axis k (cell * n^d + j), one per thread.  Matrix-unit
+// form: ordered so that every 16 threads take lines of different bank pairs as far as there are
+// any left (neighbouring lines along x are n nodes apart, 2 to 8 of 16 in the same bank pair).
+template <int DIM, int N, int CPB, int VC, typename R>
+struct LineMap {
+    static constexpr int NN = cpow(N + 1, DIM), ACT = CPB * NN;
+    uint16_t line[DIM][ACT];
+    constexpr LineMap() : line{} {
+        using L = PredLds<DIM, N, VC, R>;
+        for (int k = 0; k < DIM; k++) {
+            if (!L::MAT) {
+                for (int i = 0; i < ACT; i++) line[k][i] = (uint16_t)i;
+                continue;
+            }
+            // lines by bank pair: first[b] .. in order, next[i] the following one
+            int head[16] = {}, left[16] = {};
+            uint16_t next[ACT] = {};
+            for (int b = 0; b < 16; b++) head[b] = -1;
+            for (int i = ACT - 1; i >= 0; i--) {
+                const int b = (i / NN * (L::CELL / 2) + L::line(k, i % NN)) % 16;
+                next[i] = (uint16_t)(head[b] + 1);
+                head[b] = i;
+                left[b]++;
+            }
+            for (int i = 0; i < ACT;) {
+                // one line of each of the bank pairs with most lines left, largest first
+                bool used[16] = {};
+                int m = 0;
+                for (; m < 16 && i < ACT; m++) {
+                    int best = -1;
+                    for (int b = 0; b < 16; b++)
+                        if (!used[b] && left[b] && (best < 0 || left[b] > left[best])) best = b;
+                    if (best < 0) {
+                        for (int b = 0; b < 16; b++) used[b] = false;
+                        m--;
+                        continue;
+                    }
+                    used[best] = true;
+                    line[k][i++] = (uint16_t)head[best];
+                    head[best] = (int)next[head[best]] - 1;
+                    left[best]--;
+                }
+            }
+        }
+    }
+};
+template <int DIM, int N, int CPB, int VC, typename R>
+static __device__ const LineMap<DIM, N, CPB, VC, R> line_map{};
+template <typename R> struct PairOf;
+template <> struct PairOf<float> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct PairOf<double> { typedef double type __attribute__((ext_vector_type(2))); };
+// f(v, x) of every variable v < VC of the point (one or two per access)
+template <typename L, int VC, typename R, typename F>
+__device__ __forceinline__ void lds_get(const R *X, int pt, F f) {
+#pragma unroll
+    for (int v = 0; v < VC; v += 2) {
+        if (L::paired(v)) {
+            const auto x = *reinterpret_cast<const typename PairOf<R>::type *>(X + L::at(v) + 2 * pt);
+            f(v, x[0]);
+            f(v + 1, x[1]);
+        } else {
+            f(v, X[L::at(v) + pt]);
+            if (v + 1 < VC) f(v + 1, X[L::at(v + 1) + pt]);
+        }
+    }
+}
+// the point's variables v < VC set to f(v)
+template <typename L, int VC, typename R, typename F>
+__device__ __forceinline__ void lds_put(R *X, int pt, F f) {
+#pragma unroll
+    for (int v = 0; v < VC; v += 2) {
+        if (L::paired(v)) {
+            typename PairOf<R>::type x;
+            x[0] = f(v);
+            x[1] = f(v + 1);
+            *reinterpret_cast<typename PairOf<R>::type *>(X + L::at(v) + 2 * pt) = x;
+        } else {
+            X[L::at(v) + pt] = f(v);
+            if (v + 1 < VC) X[L::at(v + 1) + pt] = f(v + 1);
+        }
+    }
+}
+// y = D x of one line in a lane's registers
+template <int N>
+__device__ __forceinline__ void mat_line(const MatOps<N> &M, const float *x, float *y) {
+    using O = MatOps<N>;
+    constexpr int n = O::n, h = O::h;
+    if constexpr (O::EO) {
+        float e[O::hu], o[h];
+#pragma unroll
+        for (int b = 0; b < h; b++) {
+            e[b] = x[b] + x[n - 1 - b];
+            o[b] = x[b] - x[n - 1 - b];
+        }
+        if constexpr (n % 2) e[h] = x[h];
+        mvec pe[O::GE] = {}, po[O::GO] = {};
+        mat_cols<0, O::hu, O::GE>(M.d, e, pe);
+        mat_cols<O::OB, h, O::GO>(M.d, o, po);
+#pragma unroll
+        for (int i = 0; i < h; i++) {
+            y[i] = po[i / 4][i % 4] + pe[i / 4][i % 4];
+            y[n - 1 - i] = po[i / 4][i % 4] - pe[i / 4][i % 4];
+        }
+        if constexpr (n % 2) y[h] = po[h / 4][h % 4];
+    } else {
+        mvec acc[O::G] = {};
+        mat_cols<0, n, O::G>(M.d, x, acc);
+#pragma unroll
+        for (int i = 0; i < n; i++) y[i] = acc[i / 4][i % 4];
+    }
+}
+// Contraction with the derivative matrix along axis k of the line that starts at point pt, of
+// every variable, in place.  The matrix unit ignores the execution mask, so a wave enters as a
+// whole; lanes that have no line of their own read one and store nothing.
+template <int DIM, int N, int VC>
+__device__ __forceinline__ void mat_lines(float *X, int k, int pt, bool store, const MatOps<N> &M) {
+    using L = PredLds<DIM, N, VC, float>;
+    constexpr int n = N + 1;
+    typedef PairOf<float>::type pair;
+    const int st = L::stride(k);
+#pragma unroll
+    for (int v = 0; v < VC; v += 2) {
+        // compiler barrier: one pair's line in registers at a time
+        __asm__ volatile("" ::: "memory");
+        float x[2][n], y[2][n];
+        if (L::paired(v)) {
+            pair *line = reinterpret_cast<pair *>(X + L::at(v)) + pt;
+#pragma unroll
+            for (int b = 0; b < n; b++) {
+                const pair p = line[b * st];
+                x[0][b] = p[0];
+                x[1][b] = p[1];
+            }
+            mat_line<N>(M, x[0], y[0]);
+            mat_line<N>(M, x[1], y[1]);
+            if (store) {
+#pragma unroll
+                for (int b = 0; b < n; b++) line[b * st] = pair{y[0][b], y[1][b]};
+            }
+        } else {
+            float *line = X + L::at(v) + pt;
+#pragma unroll
+            for (int b = 0; b < n; b++) x[0][b] = line[b * st];
+            mat_line<N>(M, x[0], y[0]);
+            if (store) {
+#pragma unroll
+                for (int b = 0; b < n; b++) line[b * st] = y[0][b];
+            }
+        }
+    }
+}
+
 // Contraction along axis k of every line held in LDS: line[i] <- c * sum_b M[i][b] line[b]
 // (c only if SCALE).  One work item handles the same line of LV variables (independent FMA
 // chains sharing each operator entry; for long lines LV is 2 (FP32) or 1 (FP64) to bound
 // register use).
 // EO: M is the derivative matrix on symmetric nodes, applied through its even / odd parts
 // E, O (half-size products on x_b +- x_{n-1-b}: n^2/2 + 2n operations instead of n^2).
-template <int DIM, int N, int CPB, int VC, int BS, typename R, bool EO = false, bool SCALE = true>
-__device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int lstride_s, const R (*M)[MAXN], R c,
-                                          int tid, int nvalid, const R (*E)[MAXN / 2 + 1] = nullptr,
+template <int DIM, int N, int CPB, int VC, int BS, typename R, bool EO>
+__device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int lstride_s, const R (*M)[MAXN], int tid,
+                                          int nvalid, const R (*E)[MAXN / 2 + 1] = nullptr,
                                           const R (*O)[MAXN / 2] = nullptr) {
     constexpr int n = N + 1, NN = cpow(n, DIM), NST = NN * n;
     constexpr int LV = (n >= 8) ? (sizeof(R) == 8 ? 1 : 2) : VC;
@@ -108,8 +328,8 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 for (int vv = 0; vv < LV; vv++)
                     if (v0 + vv < nvalid) {
                         const R yi = po[vv] + pe[vv], yr = po[vv] - pe[vv];
-                        line0[vv * NST + i * st] = SCALE ? c * yi : yi;
-                        line0[vv * NST + (n - 1 - i) * st] = SCALE ? c * yr : yr;
+                        line0[vv * NST + i * st] = yi;
+                        line0[vv * NST + (n - 1 - i) * st] = yr;
                     }
             }
             if constexpr (n % 2) {
@@ -124,7 +344,7 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 }
 #pragma unroll
                 for (int vv = 0; vv < LV; vv++)
-                    if (v0 + vv < nvalid) line0[vv * NST + h * st] = SCALE ? c * acc[vv] : acc[vv];
+                    if (v0 + vv < nvalid) line0[vv * NST + h * st] = acc[vv];
             }
         } else {
 #pragma unroll
@@ -140,7 +360,7 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 }
 #pragma unroll
                 for (int vv = 0; vv < LV; vv++)
-                    if (v0 + vv < nvalid) line0[vv * NST + i * st] = SCALE ? c * acc[vv] : acc[vv];
+                    if (v0 + vv < nvalid) line0[vv * NST + i * st] = acc[vv];
             }
         }
     }
@@ -153,29 +373,39 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
 // constant F(c), so the Picard iteration, the volume term and the traces are those of the
 // deviations, and FP32 rounding is relative to the deviation instead of the state.
 template <int DIM, int N, bool VOL, typename R, bool DEV = false, int TB = Tune<DIM, N, sizeof(R) == 4>::pred_tb>
-__device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, int64_t vb0, int64_t vbs) {
+__device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, int64_t vb0, int64_t vbs) {
     static_assert(!DEV || sizeof(R) == 4, "the deviation form is an FP32 form");
     using S = PredShape<DIM, N, R, TB>;
     const R gamma = (R)gamma_d;
     constexpr int n = S::n, NV = S::NV, NN = S::NN, NST = S::NST, NFN = S::NFN, CPB = S::CPB, VC = S::VC;
-    __shared__ R X[CPB * VC * NST];
+    using L = PredLds<DIM, N, VC, R>;
+    constexpr bool MAT = L::MAT;
+    __shared__ __align__(16) R X[CPB * L::CELL];
     // operators staged in LDS and read as wave-uniform broadcasts inside the loops (kept
     // out of registers: the n x n matrices would otherwise be hoisted into VGPRs)
-    __shared__ R Ds[n][MAXN], Kws[n][MAXN], Dvs[n][MAXN];
+    __shared__ R Dvs[n][MAXN], ws[MAXN], Bs[2][MAXN];
     // the spatial contractions use the even / odd form where it saves work (n >= 6)
     constexpr bool EO = n >= 6;
-    __shared__ R Es[EO ? MAXN / 2 : 1][MAXN / 2 + 1], Os[EO ? MAXN / 2 + 1 : 1][MAXN / 2];
+    __shared__ R Ds[MAT ? 1 : n][MAXN], Kws[MAT ? 1 : n][MAXN];
+    __shared__ R Es[EO && !MAT ? MAXN / 2 : 1][MAXN / 2 + 1], Os[EO && !MAT ? MAXN / 2 + 1 : 1][MAXN / 2];
 
     const int tid = threadIdx.x;
     const int lc = tid / NN, a = tid % NN;
     const double dt = *A.dt;
     for (int i = tid; i < n * n; i += S::BS) {
         const int r = i / n, cc = i % n;
-        Ds[r][cc] = A.D[r * MAXN + cc];
-        Kws[r][cc] = A.Kw[r * MAXN + cc];
+        if constexpr (!MAT) {
+            Ds[r][cc] = A.D[r * MAXN + cc];
+            Kws[r][cc] = A.Kw[r * MAXN + cc];
+        }
         Dvs[r][cc] = VOL ? A.Dvol[r * MAXN + cc] : R(0);
     }
-    if constexpr (EO) {
+    if (tid < n) {
+        ws[tid] = VOL ? A.w[tid] : R(0);
+        Bs[0][tid] = A.Lb[tid];
+        Bs[1][tid] = A.Rb[tid];
+    }
+    if constexpr (EO && !MAT) {
         for (int i = tid; i < (MAXN / 2) * (MAXN / 2 + 1); i += S::BS) {
             Es[i / (MAXN / 2 + 1)][i % (MAXN / 2 + 1)] = A.DE[i];
             Os[i / (MAXN / 2)][i % (MAXN / 2)] = A.DO[i];
@@ -185,10 +415,42 @@ __device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, 
     const R(*D)[MAXN] = Ds;
     const R(*Kw)[MAXN] = Kws;
     const R(*Dvol)[MAXN] = Dvs;
+    MatOps<N> M;
+    if constexpr (MAT) {
+        const int row = tid & 3, col = (tid & 63) >> 2;
+#pragma unroll
+        for (int g = 0; g < MatOps<N>::G; g++) {
+            const int r = 4 * g + row;
+            M.kw[g] = (r < n && col < n) ? A.Kw[r * MAXN + col] : R(0);
+        }
+#pragma unroll
+        for (int g = 0; g < MatOps<N>::GD; g++) {
+            const int r = 4 * g + row, oc = col - MatOps<N>::OB;
+            if constexpr (EO) {
+                M.d[g] = (r < n / 2 && col < n - n / 2) ? A.DE[r * (MAXN / 2 + 1) + col]
+                         : (r < n - n / 2 && oc >= 0 && oc < n / 2) ? A.DO[r * (MAXN / 2) + oc] : R(0);
+            } else {
+                M.d[g] = (r < n && col < n) ? A.D[r * MAXN + col] : R(0);
+            }
+        }
+    }
+    // this thread's point (slice 0), and the line of each axis that it contracts (threads past the
+    // last cell: the last ones, and store nothing)
+    const bool act = tid < S::ACT;
+    const int ia = act ? tid : S::ACT - 1, la = ia % NN;
+    R *Xc = X + ia / NN * L::CELL;
+    int lcell[DIM], lj[DIM], lpt[DIM];   // its cell, its number in the cell and its first point
+#pragma unroll
+    for (int k = 0; k < DIM; k++) {
+        const int i = MAT ? line_map<DIM, N, CPB, VC, R>.line[k][ia] : ia;
+        lcell[k] = i / NN;
+        lj[k] = i % NN;
+        lpt[k] = L::line(k, lj[k]);
+    }
     // persistent over blocks of CPB cells (uniform per block: barriers stay legal)
     for (int64_t vb = vb0; vb * CPB < ncell; vb += vbs) {
     const int64_t c = vb * CPB + lc;
-    const bool owner = (tid < S::ACT) && (c < ncell);
+    const bool owner = act && (c < ncell);
 
     R u0[NV], q[NV][n], Sacc[NV][n];
     DevRef<DIM, R> cref;
@@ -229,6 +491,10 @@ __device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, 
     auto sweep = [&](auto first_c) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_c)::value;
         constexpr int NT = FIRST ? 1 : n;   // time slices computed
+        // (opaque per sweep: the LDS addresses are formed where they are used instead of being
+        // held, and spilled, across the sweeps)
+        int pt = la;
+        __asm__ volatile("" : "+v"(pt));
         // 1/rho of every node of the pencil, shared by the fluxes of all axes (for long
         // FP64 pencils recomputed per axis instead, to stay within 256 registers)
         constexpr bool CACHE_IRHO = n < 8 || sizeof(R) == 4;
@@ -284,25 +550,36 @@ __device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, 
                             for (int j = 0; j < DIM; j++) F[1 + j] = q[1 + j][t] * un + (j == k ? prt : R(0));
                             F[NV - 1] = un * (q[NV - 1][t] + prt);
                         }
-#pragma unroll
-                        for (int vv = 0; vv < VC; vv++)
-                            if (v0 + vv < NV) X[(lc * VC + vv) * NST + a + NN * t] = F[v0 + vv];
+                        lds_put<L, VC>(Xc, pt + L::SS * t, [&](int vv) __attribute__((always_inline)) {
+                            return v0 + vv < NV ? F[v0 + vv] : R(0);
+                        });
                     }
                 }
                 __syncthreads();
-                lds_lines<DIM, N, CPB, VC, S::BS, R, EO, false>(X, k, FIRST ? NN / n : NN, FIRST ? 0 : NN, D, R(1),
-                                                                tid, NV - v0 < VC ? NV - v0 : VC, Es, Os);
+                if constexpr (MAT) {
+                    constexpr int NIT = FIRST ? CPB * (NN / n) : S::ACT;   // lines
+                    int cell = lcell[k], lp = lpt[k];
+                    if constexpr (FIRST) {
+                        const int it = tid < NIT ? tid : NIT - 1;
+                        cell = it / (NN / n);
+                        lp = L::line(k, it % (NN / n));
+                    }
+                    if (__builtin_amdgcn_readfirstlane(tid) < NIT)
+                        mat_lines<DIM, N, VC>(X + cell * L::CELL, k, lp, tid < NIT, M);
+                } else {
+                    lds_lines<DIM, N, CPB, VC, S::BS, R, EO>(X, k, FIRST ? NN / n : NN, FIRST ? 0 : NN, D, tid,
+                                                             NV - v0 < VC ? NV - v0 : VC, Es, Os);
+                }
                 __syncthreads();
                 // S = sum_k (dt/h_k) D_k F_k, the factor applied while accumulating
-                if (tid < S::ACT) {
+                // (the next fluxes go to the points that this thread alone has just read: no barrier)
+                if (act) {
 #pragma unroll
-                    for (int vv = 0; vv < VC; vv++)
-                        if (v0 + vv < NV)
-#pragma unroll
-                            for (int t = 0; t < n; t++) {
-                                const R xk = X[(lc * VC + vv) * NST + a + NN * (FIRST ? 0 : t)];
+                    for (int t = 0; t < n; t++)
+                        lds_get<L, VC>(Xc, pt + L::SS * (FIRST ? 0 : t), [&](int vv, R xk) __attribute__((always_inline)) {
+                            if (v0 + vv < NV)
                                 Sacc[v0 + vv][t] = (k == 0) ? ck * xk : Sacc[v0 + vv][t] + ck * xk;
-                            }
+                        });
                 } else if (k == 0) {
 #pragma unroll
                     for (int vv = 0; vv < VC; vv++)
@@ -310,24 +587,35 @@ __device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, 
 #pragma unroll
                             for (int t = 0; t < n; t++) Sacc[v0 + vv][t] = 0;
                 }
-                __syncthreads();
+                __asm__ volatile("" ::: "memory");
             }
         }
-        // time contraction in registers (Kw row s broadcast from LDS, shared by the variables)
+        // time contraction in registers: on the matrix unit, or with row s of Kw broadcast from
+        // LDS and shared by the variables
+        if constexpr (MAT) {
 #pragma unroll
-        for (int s = 0; s < n; s++) {
-            __asm__ volatile("" ::: "memory");
-            R acc[NV];
+            for (int v = 0; v < NV; v++) {
+                mvec acc[MatOps<N>::G] = {};
+                mat_cols<0, n, MatOps<N>::G>(M.kw, Sacc[v], acc);
 #pragma unroll
-            for (int v = 0; v < NV; v++) acc[v] = 0;
-#pragma unroll
-            for (int t = 0; t < n; t++) {
-                const R kst = Kw[s][t];
-#pragma unroll
-                for (int v = 0; v < NV; v++) acc[v] += kst * Sacc[v][t];
+                for (int s = 0; s < n; s++) q[v][s] = u0[v] - acc[s / 4][s % 4];
             }
+        } else {
 #pragma unroll
-            for (int v = 0; v < NV; v++) q[v][s] = u0[v] - acc[v];
+            for (int s = 0; s < n; s++) {
+                __asm__ volatile("" ::: "memory");
+                R acc[NV];
+#pragma unroll
+                for (int v = 0; v < NV; v++) acc[v] = 0;
+#pragma unroll
+                for (int t = 0; t < n; t++) {
+                    const R kst = Kw[s][t];
+#pragma unroll
+                    for (int v = 0; v < NV; v++) acc[v] += kst * Sacc[v][t];
+                }
+#pragma unroll
+                for (int v = 0; v < NV; v++) q[v][s] = u0[v] - acc[v];
+            }
         }
     };
     if (A.iters > 0) sweep(std::true_type{});
@@ -335,45 +623,125 @@ __device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, 
 
     // ---- volume term of eq. (pde.nc.gw2), divided by the diagonal mass:
     //   (dt/h_k) sum_b [w_b D[b][a_k] / w_{a_k}] sum_s w_s F_k(q(a|b, s))
+    R Fi[VOL ? DIM : 1][NV];   // sum_s w_s F_k(q(a, s))
     if constexpr (VOL) {
+#pragma unroll
+        for (int v = 0; v < NV; v++)
+#pragma unroll
+            for (int k = 0; k < DIM; k++) Fi[k][v] = 0;
+#pragma unroll
+        for (int t = 0; t < n; t++) {
+            __builtin_amdgcn_sched_barrier(0);
+            R qt[NV], F[NV];
+#pragma unroll
+            for (int v = 0; v < NV; v++) qt[v] = q[v][t];
+            const R ir = recip(DEV ? cref.q[0] + qt[0] : qt[0]);
+            R pt_;
+            if constexpr (DEV) pt_ = dev_pressure<DIM, R>(cref, qt, ir, gamma);
+            else {
+                R ke = 0;
+#pragma unroll
+                for (int j = 0; j < DIM; j++) ke += qt[1 + j] * qt[1 + j];
+                pt_ = (gamma - R(1)) * (qt[NV - 1] - quotient(R(0.5) * ke, qt[0], ir));
+            }
+#pragma unroll
+            for (int k = 0; k < DIM; k++) {
+                if constexpr (DEV) {
+                    dev_flux<DIM, R>(k, cref, qt, ir, pt_, F);
+                } else {
+                    const R un = quotient(qt[1 + k], qt[0], ir);
+                    F[0] = qt[1 + k];
+#pragma unroll
+                    for (int j = 0; j < DIM; j++) F[1 + j] = qt[1 + j] * un + (j == k ? pt_ : R(0));
+                    F[NV - 1] = un * (qt[NV - 1] + pt_);
+                }
+#pragma unroll
+                for (int v = 0; v < NV; v++) Fi[k][v] += ws[t] * F[v];
+            }
+        }
+        // formed here, not where they are used: the pencils end with the traces
+#pragma unroll
+        for (int k = 0; k < DIM; k++)
+#pragma unroll
+            for (int v = 0; v < NV; v++) __asm__ volatile("" : "+v"(Fi[k][v]));
+    }
+
+    // ---- face traces: q at xi_k = 0 / 1 per tangential node and time node; every thread takes
+    // the line of each axis that it contracts in the sweeps
+    for (int v0 = 0; v0 < NV; v0 += VC) {
+        int pt = la;
+        __asm__ volatile("" : "+v"(pt));
+        if (act) {
+#pragma unroll
+            for (int s = 0; s < n; s++)
+                lds_put<L, VC>(Xc, pt + L::SS * s, [&](int vv) __attribute__((always_inline)) {
+                    return v0 + vv < NV ? q[v0 + vv][s] : R(0);
+                });
+        }
+        __syncthreads();
+        if (act) {
+#pragma unroll
+            for (int k = 0; k < DIM; k++) {
+                const int64_t cc = vb * CPB + lcell[k];
+                const R *Xl = X + lcell[k] * L::CELL;
+                R tr[2][VC];
+#pragma unroll
+                for (int vv = 0; vv < VC; vv++) tr[0][vv] = tr[1][vv] = 0;
+#pragma unroll
+                for (int b = 0; b < n; b++) {
+                    if (b % 4 == 0) __asm__ volatile("" ::: "memory");
+                    lds_get<L, VC>(Xl, lpt[k] + b * L::stride(k), [&](int vv, R x) __attribute__((always_inline)) {
+                        tr[0][vv] += Bs[0][b] * x;
+                        tr[1][vv] += Bs[1][b] * x;
+                    });
+                }
+#pragma unroll
+                for (int side = 0; side < 2; side++)
+#pragma unroll
+                    for (int vv = 0; vv < VC; vv++)
+                        if (v0 + vv < NV && cc < ncell)
+                            A.trace[((cc * 2 * DIM + 2 * k + side) * NV + v0 + vv) * (NFN * n) + lj[k]] = tr[side][vv];
+            }
+        }
+        __syncthreads();
+    }
+    // ---- volume term: the contraction of the time-integrated fluxes (after the traces, when the
+    // pencils' registers are free)
+    if constexpr (VOL) {
+        int pt = la;
+        __asm__ volatile("" : "+v"(pt));
         R vol[NV];
 #pragma unroll
         for (int v = 0; v < NV; v++) vol[v] = 0;
+        // every thread contracts for its own node; a slice of X per axis and chunk of variables,
+        // used again only after a barrier
+        constexpr int NCH = (NV + VC - 1) / VC;
 #pragma unroll
         for (int k = 0; k < DIM; k++) {
             const R ck = (R)(dt * A.dth[k]);
-            R Fi[NV];
+            const int ak = (k == 0 ? la : (k == 1 ? la / n : la / (n * n))) % n, l0 = pt - ak * L::stride(k);
 #pragma unroll
-            for (int v = 0; v < NV; v++) Fi[v] = 0;
+            for (int ch = 0; ch < NCH; ch++) {
+                const int i = k * NCH + ch, v0 = ch * VC, sl = L::SS * (i % n);
+                if (act)
+                    lds_put<L, VC>(Xc, pt + sl, [&](int vv) __attribute__((always_inline)) {
+                        return v0 + vv < NV ? Fi[k][v0 + vv] : R(0);
+                    });
+                __syncthreads();
+                R acc[VC];
 #pragma unroll
-            for (int t = 0; t < n; t++) {
-                R qt[NV], F[NV];
+                for (int vv = 0; vv < VC; vv++) acc[vv] = 0;
 #pragma unroll
-                for (int v = 0; v < NV; v++) qt[v] = q[v][t];
-                if constexpr (DEV) {
-                    const R ir = recip(cref.q[0] + qt[0]);
-                    dev_flux<DIM, R>(k, cref, qt, ir, dev_pressure<DIM, R>(cref, qt, ir, gamma), F);
-                } else {
-                    euler_flux<DIM, R>(k, qt, F, gamma);
+                for (int b = 0; b < n; b++) {
+                    if (b % 4 == 0) __asm__ volatile("" ::: "memory");
+                    const R d = Dvol[ak][b];
+                    lds_get<L, VC>(Xc, l0 + sl + b * L::stride(k),
+                                   [&](int vv, R x) __attribute__((always_inline)) { acc[vv] += d * x; });
                 }
 #pragma unroll
-                for (int v = 0; v < NV; v++) Fi[v] += A.w[t] * F[v];
-            }
-            for (int v0 = 0; v0 < NV; v0 += VC) {
-                if (tid < S::ACT) {
-#pragma unroll
-                    for (int vv = 0; vv < VC; vv++)
-                        if (v0 + vv < NV) X[(lc * VC + vv) * NST + a] = Fi[v0 + vv];
-                }
-                __syncthreads();
-                lds_lines<DIM, N, CPB, VC, S::BS, R>(X, k, NN / n, 0, Dvol, ck, tid, NV - v0 < VC ? NV - v0 : VC);
-                __syncthreads();
-                if (tid < S::ACT) {
-#pragma unroll
-                    for (int vv = 0; vv < VC; vv++)
-                        if (v0 + vv < NV) vol[v0 + vv] += X[(lc * VC + vv) * NST + a];
-                }
-                __syncthreads();
+                for (int vv = 0; vv < VC; vv++)
+                    if (v0 + vv < NV) vol[v0 + vv] += ck * acc[vv];
+                if ((i + 1) % n == 0 || i + 1 == DIM * NCH) __syncthreads();
             }
         }
         if (owner) {
@@ -383,47 +751,6 @@ __device__ void pred_cells(const PredArgs<R> &A, double gamma_d, int64_t ncell, 
                 A.vol_out[(A.cell0 + c) * NN + (int64_t)v * A.in_vstride + a] =
                     A.in[c * A.in_cstride + v * A.in_vstride + a] + (double)vol[v];
         }
-    }
-
-    // ---- face traces: q at xi_k = 0 / 1 per tangential node and time node
-    for (int v0 = 0; v0 < NV; v0 += VC) {
-        if (tid < S::ACT) {
-#pragma unroll
-            for (int vv = 0; vv < VC; vv++)
-                if (v0 + vv < NV)
-#pragma unroll
-                    for (int s = 0; s < n; s++) X[(lc * VC + vv) * NST + a + NN * s] = q[v0 + vv][s];
-        }
-        __syncthreads();
-        const int nitems = CPB * VC * 2 * DIM * NFN * n;
-        for (int it = tid; it < nitems; it += S::BS) {
-            const int lcl = it / (VC * 2 * DIM * NFN * n);
-            int rem0 = it % (VC * 2 * DIM * NFN * n);
-            const int vv = rem0 / (2 * DIM * NFN * n);
-            rem0 %= 2 * DIM * NFN * n;
-            const int face = rem0 / (NFN * n);
-            const int j = rem0 % (NFN * n);   // ap + NFN*s
-            const int s = j / NFN, ap = j % NFN;
-            const int k = face >> 1, side = face & 1;
-            const int64_t cc = vb * CPB + lcl;
-            if (cc >= ncell || v0 + vv >= NV) continue;
-            int base = 0, rem = ap, mul = 1;
-#pragma unroll
-            for (int jj = 0; jj < DIM; jj++) {
-                if (jj == k) { mul *= n; continue; }
-                base += (rem % n) * mul;
-                rem /= n;
-                mul *= n;
-            }
-            const R *line = &X[(lcl * VC + vv) * NST + NN * s + base];
-            const int st = (k == 0) ? 1 : (k == 1 ? n : n * n);
-            const R *Bv = side ? A.Rb : A.Lb;
-            R acc = 0;
-#pragma unroll
-            for (int b = 0; b < n; b++) acc += Bv[b] * line[b * st];
-            A.trace[((cc * 2 * DIM + face) * NV + v0 + vv) * (NFN * n) + j] = acc;
-        }
-        __syncthreads();
     }
     }  // persistent loop
 }
