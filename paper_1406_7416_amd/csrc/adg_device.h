@@ -139,6 +139,21 @@ __device__ __forceinline__ void coords_of(const Prob &P, int64_t c, int *ci) {
     ci[2] = (int)(c / ((int64_t)P.nc[0] * P.nc[1]));
 }
 
+// The same with 32-bit divisions (there are less than 2^31 cells: the cell lists hold int).
+template <int DIM>
+__device__ __forceinline__ void cell_coords(const Prob &P, int64_t c, int *ci) {
+    const uint32_t u = (uint32_t)c, n0 = (uint32_t)P.nc[0], r = u / n0;
+    ci[0] = (int)(u - r * n0);
+    if constexpr (DIM == 2) {
+        ci[1] = (int)r;
+        ci[2] = 0;
+    } else {
+        const uint32_t n1 = (uint32_t)P.nc[1];
+        ci[2] = (int)(r / n1);
+        ci[1] = (int)(r - (uint32_t)ci[2] * n1);
+    }
+}
+
 // ------------------------------------------------------------- wave reductions
 // A 32-bit value moved down by S lanes within each row of 16 lanes (DPP row_shr); a lane
 // whose source lies outside its row keeps its own value (harmless for min, max and or).
@@ -183,6 +198,53 @@ __device__ __forceinline__ double wave_min(double x) {
 }
 __device__ __forceinline__ double wave_max(double x) {
     return wave_reduce(x, [](double a, double b) { return fmax(a, b); });
+}
+
+// The upper half (swap32) or the odd rows of 16 lanes (swap16) of a exchanged with the lower half
+// or the even rows of b: min(a, b) then reduces two values at once, a's in the lower half (even
+// rows) and b's in the upper (odd rows).
+__device__ __forceinline__ void swap32(double &a, double &b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)((unsigned long long)h[0] << 32 | l[0]));
+    b = __longlong_as_double((long long)((unsigned long long)h[1] << 32 | l[1]));
+}
+__device__ __forceinline__ void swap16(double &a, double &b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)((unsigned long long)h[0] << 32 | l[0]));
+    b = __longlong_as_double((long long)((unsigned long long)h[1] << 32 | l[1]));
+}
+// op over each row of 16 lanes, in the row's last lane
+template <typename Op>
+__device__ __forceinline__ double row_reduce(double x, Op op) {
+    x = op(x, row_shr<1>(x));
+    x = op(x, row_shr<2>(x));
+    x = op(x, row_shr<4>(x));
+    return op(x, row_shr<8>(x));
+}
+// op of four values over the wave (every lane active): value {0, 2, 1, 3}[r] in the last lane of
+// row r.  42 instructions for four minima and four maxima, against 8 x 20 one after the other.
+template <typename Op>
+__device__ __forceinline__ double wave_reduce4(const double *x, Op op) {
+    double a = x[0], b = x[1], c = x[2], d = x[3];
+    swap32(a, b);
+    swap32(c, d);
+    a = op(a, b);
+    c = op(c, d);
+    swap16(a, c);
+    return row_reduce(op(a, c), op);
+}
+// minima of two values over the wave: of x in lane 15, of y in lane 47
+__device__ __forceinline__ double wave_min2(double x, double y) {
+    const auto op = [](double a, double b) { return fmin(a, b); };
+    swap32(x, y);
+    x = fmin(x, y);
+    y = x;
+    swap16(x, y);
+    return row_reduce(fmin(x, y), op);
 }
 
 // ------------------------------------------------------------- masked geometry
