@@ -160,8 +160,9 @@ __device__ __forceinline__ void face_axis(const Tables *__restrict__ T, const Pr
     bool hasL = false, hasR = false, wall = false;
     int fk = 0, ci[3] = {0, 0, 0};
     if (active) {
-        fk = (int)(fidx % nfk);
-        int64_t line = fidx / nfk;
+        // 32-bit divisions: less than 2^31 cells, so less than 2^32 faces along an axis
+        uint32_t line = (uint32_t)fidx / (uint32_t)nfk;
+        fk = (int)((uint32_t)fidx - line * (uint32_t)nfk);
         // cell coordinates, selected per axis with compile-time indices (a runtime index
         // would move the arrays to scratch memory)
         hasL = fk > 0 || P.periodic[k];
@@ -174,8 +175,9 @@ __device__ __forceinline__ void face_axis(const Tables *__restrict__ T, const Pr
                 cl[jj] = fl;
                 cr[jj] = fk;
             } else {
-                ci[jj] = (int)(line % P.nc[jj]);
-                line /= P.nc[jj];
+                const uint32_t next = line / (uint32_t)P.nc[jj];
+                ci[jj] = (int)(line - next * (uint32_t)P.nc[jj]);
+                line = next;
                 cl[jj] = cr[jj] = ci[jj];
             }
         }
@@ -193,7 +195,7 @@ __device__ __forceinline__ void face_axis(const Tables *__restrict__ T, const Pr
         const double dt = scal[0], t0 = scal[1];
         // node position on the face (for boundary states)
         double x[3] = {0, 0, 0};
-        {
+        if (!hasL || !hasR) {
             int rem = ap;
 #pragma unroll
             for (int jj = 0; jj < DIM; jj++) {
@@ -851,7 +853,7 @@ __global__ __launch_bounds__(128) void k_cell_bounds(const Tables *__restrict__ 
 __device__ __forceinline__ bool corr_flag(const Prob &P, const uint8_t *beta, const uint8_t *mask, int64_t c) {
     if (beta[c] || (mask && mask[c])) return false;
     int ci[3];
-    coords_of(P, c, ci);
+    cell_coords<3>(P, c, ci);
     for (int k = 0; k < P.dim; k++)
         for (int side = 0; side < 2; side++) {
             int nb[3] = {ci[0], ci[1], ci[2]};
