@@ -1586,8 +1586,8 @@ int adg_cfl_dt_static(const double *dev_u, int dim, int N, int64_t ncell, double
     C.stream = (hipStream_t)hip_stream;
     const int64_t nn = ipow64(N + 1, dim);
     C.lam_blocks = (int)std::min<int64_t>(ADG_STATIC_PARTIALS, std::max<int64_t>(1, (ncell * nn + 255) / 256));
+    C.dt_out = dev_dt;
     launch_lambda(C, dev_u, cfl * hmin / (dim * (2.0 * N + 1.0)));
-    launch_copy_scalar(C.B.scal, dev_dt, C.stream);
     HIPCHK(hipGetLastError());
     return ADG_OK;
 }

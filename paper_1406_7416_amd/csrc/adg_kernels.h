@@ -14,6 +14,7 @@ struct StepCtx {
     int picard_iters;
     int64_t capacity;      // pool slots
     int lam_blocks;        // blocks of the lambda reduction
+    double *dt_out = nullptr;   // second place for dt (nullptr: only scal[0])
     int precision;         // ADG_FP64, ADG_MIXED or ADG_MIXED_DEV
     int ring_only;         // bounds pass over the ghost ring only
     int64_t nring;         // ghost-ring cells
@@ -82,7 +83,6 @@ void launch_fluxcorr(const StepCtx &C, int count, int advance);
 void launch_lambda(const StepCtx &C, const double *u, double factor);
 void launch_set_scalar(const StepCtx &C, int idx, double val);
 void launch_advance_time(const StepCtx &C);
-void launch_copy_scalar(const double *src, double *dst, hipStream_t stream);
 // blocks of one problem's launch of a batch stage (predictor, face, corrector, compaction)
 int64_t stage_blocks(int stage, const Prob &P, int precision, int64_t *kb1, int64_t *kb2);
 void launch_batched(int dim, int N, int stage, const BatchLaunch &L);

@@ -2300,11 +2300,18 @@ __global__ __launch_bounds__(128) void k_fluxcorr(const Tables *__restrict__ T, 
 }
 
 // ------------------------------------------------------------------ time step
+// Largest of a workgroup's 256 values, in every thread: one barrier.
+__device__ __forceinline__ double block_max(double x, double *red) {
+    x = wave_max(x);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
 template <int DIM, int N>
 __device__ __forceinline__ void lambda_block(const Prob &P, const double *__restrict__ u, double *part, int64_t bid,
                                              int64_t nblk, const uint8_t *__restrict__ mask) {
     constexpr int n = N + 1, NV = DIM + 2, NN = cpow(n, DIM);
-    __shared__ double red[256];
+    __shared__ double red[4];
     double lam = 0.0;
     const int64_t total = P.ncell * NN;
     for (int64_t i = (int64_t)bid * 256 + threadIdx.x; i < total; i += (int64_t)nblk * 256) {
@@ -2316,13 +2323,8 @@ __device__ __forceinline__ void lambda_block(const Prob &P, const double *__rest
 #pragma unroll
         for (int k = 0; k < DIM; k++) lam = fmax(lam, fabs(q[1 + k] / q[0]) + cs);
     }
-    red[threadIdx.x] = lam;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + off]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[bid] = red[0];
+    lam = block_max(lam, red);
+    if (threadIdx.x == 0) part[bid] = lam;
 }
 template <int DIM, int N>
 __global__ __launch_bounds__(256) void k_lambda(Prob P, const double *__restrict__ u, double *part,
@@ -2330,23 +2332,21 @@ __global__ __launch_bounds__(256) void k_lambda(Prob P, const double *__restrict
     lambda_block<DIM, N>(P, u, part, blockIdx.x, gridDim.x, mask);
 }
 
-__device__ __forceinline__ void dt_final_block(const double *part, int nparts, double *scal, double factor) {
-    __shared__ double red[256];
+// dt into scal[0] and, if given, out[0]
+__device__ __forceinline__ void dt_final_block(const double *part, int nparts, double *scal, double factor,
+                                               double *out = nullptr) {
+    __shared__ double red[4];
     double lam = 0.0;
     for (int i = threadIdx.x; i < nparts; i += 256) lam = fmax(lam, part[i]);
-    red[threadIdx.x] = lam;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + off]);
-        __syncthreads();
-    }
+    lam = block_max(lam, red);
     if (threadIdx.x == 0) {
-        scal[2] = red[0];
-        scal[0] = factor / red[0];
+        scal[2] = lam;
+        scal[0] = factor / lam;
+        if (out) out[0] = factor / lam;
     }
 }
-static __global__ void k_dt_final(const double *part, int nparts, double *scal, double factor) {
-    dt_final_block(part, nparts, scal, factor);
+static __global__ void k_dt_final(const double *part, int nparts, double *scal, double factor, double *out) {
+    dt_final_block(part, nparts, scal, factor, out);
 }
 
 static __global__ void k_set_scalar(double *scal, int idx, double val) { scal[idx] = val; }
@@ -2746,7 +2746,8 @@ struct Launch {
         int nb = (int)((total + 255) / 256);
         if (nb > C.lam_blocks) nb = C.lam_blocks;
         hipLaunchKernelGGL((k_lambda<DIM, N>), dim3(nb), dim3(256), 0, C.stream, C.P, u, C.B.lam_part, C.B.mask);
-        hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(256), 0, C.stream, C.B.lam_part, nb, C.B.scal, factor);
+        hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(256), 0, C.stream, C.B.lam_part, nb, C.B.scal, factor,
+                           C.dt_out);
     }
 };
 
