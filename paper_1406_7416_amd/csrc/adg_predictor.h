@@ -23,7 +23,10 @@ namespace adg {
 // Measured against contractions on the vector unit, 4-byte accesses and items spread over the
 // threads (FP32): 2D N = 5, 400 x 100 cells 246 -> 192 us; N = 4, 131 x 75 41.9 -> 31.2 us; N = 3,
 // 48 problems 474 -> 302 us; N = 9, 64 x 64 240 -> 232 us; 3D N = 3, 128^3 17.9 -> 12.7 ms.  FP64
-// (traces, volume term and barriers only): 3D N = 3, 64^3 4.63 -> 4.05 ms.
+// (traces, volume term and barriers only): 3D N = 3, 64^3 4.63 -> 4.05 ms.  FP64 then spent most of
+// its LDS time on operator entries broadcast to the lanes (2D N = 9: 1650 of 2290 cycles per wave and
+// sweep); from the scalar cache they cost none: vortex N = 9, 32 x 32 cells, Osher flux, 5 steps
+// 941 -> 751 us; 12 problems N = 3..5, 5 steps 4.29 -> 4.08 ms.
 template <int DIM, int N, typename R = double, int TB = Tune<DIM, N, sizeof(R) == 4>::pred_tb>
 struct PredShape;
 
@@ -258,6 +261,23 @@ __device__ __forceinline__ void mat_lines(float *X, int k, int pt, bool store, c
     }
 }
 
+// Operator entries of the vector-unit form, the same for every lane: read through the scalar cache.
+// The pointer is made uniform, and opaque at every use, so that a row is loaded where it is used
+// instead of all rows being held (and spilled) across the sweeps.
+template <typename R> using OpPtr = const R __attribute__((address_space(4))) *;
+template <typename R>
+__device__ __forceinline__ OpPtr<R> op_ptr(const R *p) {
+    const uint64_t b = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return (OpPtr<R>)((uint64_t)hi << 32 | lo);
+}
+template <typename R>
+__device__ __forceinline__ OpPtr<R> here(OpPtr<R> p) {
+    __asm__ volatile("" : "+s"(p));
+    return p;
+}
+
 // Contraction along axis k of every line held in LDS: line[i] <- c * sum_b M[i][b] line[b]
 // (c only if SCALE).  One work item handles the same line of LV variables (independent FMA
 // chains sharing each operator entry; for long lines LV is 2 (FP32) or 1 (FP64) to bound
@@ -265,9 +285,8 @@ __device__ __forceinline__ void mat_lines(float *X, int k, int pt, bool store, c
 // EO: M is the derivative matrix on symmetric nodes, applied through its even / odd parts
 // E, O (half-size products on x_b +- x_{n-1-b}: n^2/2 + 2n operations instead of n^2).
 template <int DIM, int N, int CPB, int VC, int BS, typename R, bool EO>
-__device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int lstride_s, const R (*M)[MAXN], int tid,
-                                          int nvalid, const R (*E)[MAXN / 2 + 1] = nullptr,
-                                          const R (*O)[MAXN / 2] = nullptr) {
+__device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int lstride_s, OpPtr<R> M, int tid,
+                                          int nvalid, OpPtr<R> E, OpPtr<R> O) {
     constexpr int n = N + 1, NN = cpow(n, DIM), NST = NN * n;
     constexpr int LV = (n >= 8) ? (sizeof(R) == 8 ? 1 : 2) : VC;
     constexpr int NG = (VC + LV - 1) / LV;   // variable groups per line
@@ -312,7 +331,7 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 for (int vv = 0; vv < LV; vv++) pe[vv] = po[vv] = 0;
 #pragma unroll
                 for (int b = 0; b < h; b++) {
-                    const R me = E[i][b], mo = O[i][b];
+                    const R me = E[i * (MAXN / 2 + 1) + b], mo = O[i * (MAXN / 2) + b];
 #pragma unroll
                     for (int vv = 0; vv < LV; vv++) {
                         pe[vv] += me * e[vv][b];
@@ -320,7 +339,7 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                     }
                 }
                 if constexpr (n % 2) {
-                    const R mm = E[i][h];
+                    const R mm = E[i * (MAXN / 2 + 1) + h];
 #pragma unroll
                     for (int vv = 0; vv < LV; vv++) pe[vv] += mm * xb[vv][h];
                 }
@@ -338,7 +357,7 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 for (int vv = 0; vv < LV; vv++) acc[vv] = 0;
 #pragma unroll
                 for (int b = 0; b < h; b++) {
-                    const R mo = O[h][b];
+                    const R mo = O[h * (MAXN / 2) + b];
 #pragma unroll
                     for (int vv = 0; vv < LV; vv++) acc[vv] += mo * o[vv][b];
                 }
@@ -354,7 +373,7 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 for (int vv = 0; vv < LV; vv++) acc[vv] = 0;
 #pragma unroll
                 for (int b = 0; b < n; b++) {
-                    const R m = M[i][b];
+                    const R m = M[i * MAXN + b];
 #pragma unroll
                     for (int vv = 0; vv < LV; vv++) acc[vv] += m * xb[vv][b];
                 }
@@ -381,23 +400,15 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
     using L = PredLds<DIM, N, VC, R>;
     constexpr bool MAT = L::MAT;
     __shared__ __align__(16) R X[CPB * L::CELL];
-    // operators staged in LDS and read as wave-uniform broadcasts inside the loops (kept
-    // out of registers: the n x n matrices would otherwise be hoisted into VGPRs)
     __shared__ R Dvs[n][MAXN], ws[MAXN], Bs[2][MAXN];
     // the spatial contractions use the even / odd form where it saves work (n >= 6)
     constexpr bool EO = n >= 6;
-    __shared__ R Ds[MAT ? 1 : n][MAXN], Kws[MAT ? 1 : n][MAXN];
-    __shared__ R Es[EO && !MAT ? MAXN / 2 : 1][MAXN / 2 + 1], Os[EO && !MAT ? MAXN / 2 + 1 : 1][MAXN / 2];
 
     const int tid = threadIdx.x;
     const int lc = tid / NN, a = tid % NN;
     const double dt = *A.dt;
     for (int i = tid; i < n * n; i += S::BS) {
         const int r = i / n, cc = i % n;
-        if constexpr (!MAT) {
-            Ds[r][cc] = A.D[r * MAXN + cc];
-            Kws[r][cc] = A.Kw[r * MAXN + cc];
-        }
         Dvs[r][cc] = VOL ? A.Dvol[r * MAXN + cc] : R(0);
     }
     if (tid < n) {
@@ -405,15 +416,8 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
         Bs[0][tid] = A.Lb[tid];
         Bs[1][tid] = A.Rb[tid];
     }
-    if constexpr (EO && !MAT) {
-        for (int i = tid; i < (MAXN / 2) * (MAXN / 2 + 1); i += S::BS) {
-            Es[i / (MAXN / 2 + 1)][i % (MAXN / 2 + 1)] = A.DE[i];
-            Os[i / (MAXN / 2)][i % (MAXN / 2)] = A.DO[i];
-        }
-    }
     __syncthreads();
-    const R(*D)[MAXN] = Ds;
-    const R(*Kw)[MAXN] = Kws;
+    const OpPtr<R> D = op_ptr(A.D), Kw = op_ptr(A.Kw), DE = op_ptr(A.DE), DO = op_ptr(A.DO);
     const R(*Dvol)[MAXN] = Dvs;
     MatOps<N> M;
     if constexpr (MAT) {
@@ -567,8 +571,8 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
                     if (__builtin_amdgcn_readfirstlane(tid) < NIT)
                         mat_lines<DIM, N, VC>(X + cell * L::CELL, k, lp, tid < NIT, M);
                 } else {
-                    lds_lines<DIM, N, CPB, VC, S::BS, R, EO>(X, k, FIRST ? NN / n : NN, FIRST ? 0 : NN, D, tid,
-                                                             NV - v0 < VC ? NV - v0 : VC, Es, Os);
+                    lds_lines<DIM, N, CPB, VC, S::BS, R, EO>(X, k, FIRST ? NN / n : NN, FIRST ? 0 : NN, here(D), tid,
+                                                             NV - v0 < VC ? NV - v0 : VC, here(DE), here(DO));
                 }
                 __syncthreads();
                 // S = sum_k (dt/h_k) D_k F_k, the factor applied while accumulating
@@ -603,13 +607,13 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
         } else {
 #pragma unroll
             for (int s = 0; s < n; s++) {
-                __asm__ volatile("" ::: "memory");
+                const OpPtr<R> row = here(Kw) + s * MAXN;
                 R acc[NV];
 #pragma unroll
                 for (int v = 0; v < NV; v++) acc[v] = 0;
 #pragma unroll
                 for (int t = 0; t < n; t++) {
-                    const R kst = Kw[s][t];
+                    const R kst = row[t];
 #pragma unroll
                     for (int v = 0; v < NV; v++) acc[v] += kst * Sacc[v][t];
                 }
