@@ -499,9 +499,10 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
         // held, and spilled, across the sweeps)
         int pt = la;
         __asm__ volatile("" : "+v"(pt));
-        // 1/rho of every node of the pencil, shared by the fluxes of all axes (for long
-        // FP64 pencils recomputed per axis instead, to stay within 256 registers)
-        constexpr bool CACHE_IRHO = n < 8 || sizeof(R) == 4;
+        // 1/rho of every node of the pencil, shared by the fluxes of all axes (for long FP64 pencils
+        // recomputed per axis instead, to stay within 256 registers, and for long pencils of the
+        // deviation form to stay within 128: vortex N = 9, 64 x 64 cells, 10 steps 3.41 -> 3.19 ms)
+        constexpr bool CACHE_IRHO = n < 8 || (sizeof(R) == 4 && !(DEV && n >= 8));
         R irho[CACHE_IRHO ? n : 1], pr[CACHE_IRHO ? n : 1];
         if constexpr (CACHE_IRHO) {
 #pragma unroll
@@ -532,11 +533,16 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
                     for (int t = 0; t < NT; t++) {
                         R ir;
                         if constexpr (CACHE_IRHO) ir = irho[t];
-                        else ir = recip(q[0][t]);
+                        else ir = recip(DEV ? cref.q[0] + q[0][t] : q[0][t]);
                         const R un = q[1 + k][t] * ir;
                         R prt;
                         if constexpr (CACHE_IRHO) prt = pr[t];
-                        else {
+                        else if constexpr (DEV) {
+                            R dq[NV];
+#pragma unroll
+                            for (int v = 0; v < NV; v++) dq[v] = q[v][t];
+                            prt = dev_pressure<DIM, R>(cref, dq, ir, gamma);
+                        } else {
                             R ke = 0;
 #pragma unroll
                             for (int j = 0; j < DIM; j++) ke += q[1 + j][t] * q[1 + j][t];
