@@ -326,6 +326,8 @@ __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int l
                 }
 #pragma unroll
             for (int i = 0; i < h; i++) {
+                E = here(E);
+                O = here(O);
                 R pe[LV], po[LV];
 #pragma unroll
                 for (int vv = 0; vv < LV; vv++) pe[vv] = po[vv] = 0;
