@@ -278,17 +278,16 @@ __device__ __forceinline__ OpPtr<R> here(OpPtr<R> p) {
     return p;
 }
 
-// Contraction along axis k of every line held in LDS: line[i] <- c * sum_b M[i][b] line[b]
-// (c only if SCALE).  One work item handles the same line of LV variables (independent FMA
-// chains sharing each operator entry; for long lines LV is 2 (FP32) or 1 (FP64) to bound
-// register use).
+// Contraction along axis k of every line held in LDS: line[i] <- sum_b M[i][b] line[b].
+// One work item handles the same line of LV variables (independent FMA chains sharing each
+// operator entry; one variable for long lines, to bound register use).
 // EO: M is the derivative matrix on symmetric nodes, applied through its even / odd parts
 // E, O (half-size products on x_b +- x_{n-1-b}: n^2/2 + 2n operations instead of n^2).
 template <int DIM, int N, int CPB, int VC, int BS, typename R, bool EO>
 __device__ __forceinline__ void lds_lines(R *X, int k, int nlines_per_var, int lstride_s, OpPtr<R> M, int tid,
                                           int nvalid, OpPtr<R> E, OpPtr<R> O) {
     constexpr int n = N + 1, NN = cpow(n, DIM), NST = NN * n;
-    constexpr int LV = (n >= 8) ? (sizeof(R) == 8 ? 1 : 2) : VC;
+    constexpr int LV = (n >= 8) ? 1 : VC;
     constexpr int NG = (VC + LV - 1) / LV;   // variable groups per line
     const int st = (k == 0) ? 1 : (k == 1 ? n : n * n);
     const int nitems = CPB * NG * nlines_per_var;
@@ -398,7 +397,7 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
     static_assert(!DEV || sizeof(R) == 4, "the deviation form is an FP32 form");
     using S = PredShape<DIM, N, R, TB>;
     const R gamma = (R)gamma_d;
-    constexpr int n = S::n, NV = S::NV, NN = S::NN, NST = S::NST, NFN = S::NFN, CPB = S::CPB, VC = S::VC;
+    constexpr int n = S::n, NV = S::NV, NN = S::NN, NFN = S::NFN, CPB = S::CPB, VC = S::VC;
     using L = PredLds<DIM, N, VC, R>;
     constexpr bool MAT = L::MAT;
     __shared__ __align__(16) R X[CPB * L::CELL];
