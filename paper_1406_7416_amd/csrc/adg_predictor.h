@@ -751,7 +751,14 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
                 }
 #pragma unroll
                 for (int vv = 0; vv < VC; vv++)
-                    if (v0 + vv < NV) vol[v0 + vv] += ck * acc[vv];
+                    if (v0 + vv < NV) {
+                        vol[v0 + vv] += ck * acc[vv];
+                        // summed here, not in the owner's branch below: the compiler sinks the sums there
+                        // and keeps all their operands instead, 2 n of them per axis and chunk (24^3 cells
+                        // of degree 9: FP64 99.4 -> 87.6 ms, FP32 21.5 -> 17.4, deviation form 38.8 -> 35.9;
+                        // a cell in one chunk has few enough of them that the order makes no difference)
+                        if constexpr (VC < NV) __asm__ volatile("" : "+v"(vol[v0 + vv]));
+                    }
                 if ((i + 1) % n == 0 || i + 1 == DIM * NCH) __syncthreads();
             }
         }
