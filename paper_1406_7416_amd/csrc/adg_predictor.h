@@ -54,8 +54,11 @@ struct PredShape {
     static constexpr int CPB = NN <= TB ? TB / NN : 1;
     static constexpr int ACT = CPB * NN;                           // active point owners
     static constexpr int BS = ((ACT + 63) / 64) * 64;
-    static constexpr int VCMAX = 65536 / (CPB * NST * (int)sizeof(R));
-    static constexpr int VC = VCMAX < 1 ? 1 : (VCMAX > NV ? NV : VCMAX);  // vars per LDS chunk
+    // variables per LDS chunk: all where they fit 80 KB, half of a CU's LDS (a second chunk makes the
+    // pencils indexed arrays, which live in scratch: 2D N = 8 FP64, 70 KB, in chunks of three of its
+    // four variables 4.11 ms on 128 x 128 cells, in one 0.93 ms); else as many as 64 KB hold
+    static constexpr int VB = CPB * NST * (int)sizeof(R);   // LDS of one variable
+    static constexpr int VC = NV * VB <= 81920 ? NV : (VB <= 65536 ? 65536 / VB : 1);
 };
 
 // ---- FP32 contractions on the matrix unit (4x4x1, 16 blocks).  Lane l of a wave is column l % 4

@@ -74,3 +74,11 @@ def test_predictor_3d_degree_9_scratch(built, form):
     branch that stores them).  Bound: twice the pencil and the flux sums."""
     values = 2 * 5 * 10
     assert predictor(built, 3, 9, form)[".private_segment_fixed_size"] <= 2 * values * WIDTH[form]
+
+
+@pytest.mark.parametrize("N", range(1, 10))
+def test_predictor_2d_fp64_pencils_in_registers(built, N):
+    """A lane's 256 registers (168 where three waves share a SIMD) hold the pencil and the flux sums
+    of a 2D node, at most 2 x 4 x 10 values.  In chunks of variables whose loop is not unrolled
+    they are indexed arrays and live in scratch: less scratch than one pencil shows that they do not."""
+    assert predictor(built, 2, N, "fp64")[".private_segment_fixed_size"] < 4 * (N + 1) * WIDTH["fp64"]
