@@ -589,11 +589,17 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
                 // (the next fluxes go to the points that this thread alone has just read: no barrier)
                 if (act) {
 #pragma unroll
-                    for (int t = 0; t < n; t++)
+                    for (int t = 0; t < n; t++) {
+                        // one time node after the other: read ahead, the contracted values of a long
+                        // deviation pencil push its flux sums into scratch (2D N = 9: 57 -> 48 registers
+                        // spilled, 18 fewer in a sweep; vortex, 128 x 128 cells, steps of 1066 -> 1035 us;
+                        // n = 8 spills none there and is 1 % slower with it)
+                        if constexpr (DEV && DIM == 2 && n >= 9 && !FIRST) __builtin_amdgcn_sched_barrier(0);
                         lds_get<L, VC>(Xc, pt + L::SS * (FIRST ? 0 : t), [&](int vv, R xk) __attribute__((always_inline)) {
                             if (v0 + vv < NV)
                                 Sacc[v0 + vv][t] = (k == 0) ? ck * xk : Sacc[v0 + vv][t] + ck * xk;
                         });
+                    }
                 } else if (k == 0) {
 #pragma unroll
                     for (int vv = 0; vv < VC; vv++)

@@ -82,3 +82,11 @@ def test_predictor_2d_fp64_pencils_in_registers(built, N):
     of a 2D node, at most 2 x 4 x 10 values.  In chunks of variables whose loop is not unrolled
     they are indexed arrays and live in scratch: less scratch than one pencil shows that they do not."""
     assert predictor(built, 2, N, "fp64")[".private_segment_fixed_size"] < 4 * (N + 1) * WIDTH["fp64"]
+
+
+@pytest.mark.parametrize("N", [7, 8, 9])
+def test_predictor_2d_deviation_form_sweep_in_registers(built, N):
+    """A lane's 128 registers hold the pencil and the flux sums of a 2D node in the deviation form
+    (2 x 4 x 10 values); what is spilled are the values formed once per cell or kernel besides
+    them, fewer than 50 (57 with the flux sums of N = 9 among them)."""
+    assert predictor(built, 2, N, "dev")[".vgpr_spill_count"] < 50
