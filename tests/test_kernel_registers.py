@@ -90,3 +90,13 @@ def test_predictor_2d_deviation_form_sweep_in_registers(built, N):
     (2 x 4 x 10 values); what is spilled are the values formed once per cell or kernel besides
     them, fewer than 50 (57 with the flux sums of N = 9 among them)."""
     assert predictor(built, 2, N, "dev")[".vgpr_spill_count"] < 50
+
+
+@pytest.mark.parametrize("real", ["d", "f"])
+def test_corrector_of_large_cells_spills_nothing(built, real):
+    """One cell after the other in a workgroup: nothing of a cell's index arithmetic is to be kept
+    from cell to cell, and 256 registers hold the 20 values of a thread with their indices.  The
+    projection's 19 x 10 entries (380 scalar registers) are not to be held and spilled either."""
+    name = [k for k in built if k.startswith(f"_ZN3adg18k_corrector_detectILi3ELi9E{real}E")]
+    assert len(name) == 1 and built[name[0]][".vgpr_spill_count"] == 0
+    assert built[name[0]][".sgpr_spill_count"] < 380
