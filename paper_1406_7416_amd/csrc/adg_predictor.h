@@ -407,6 +407,8 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
     __shared__ R Dvs[n][MAXN], ws[MAXN], Bs[2][MAXN];
     // the spatial contractions use the even / odd form where it saves work (n >= 6)
     constexpr bool EO = n >= 6;
+    // workgroups of more than 512 threads leave a lane 128 registers of 4 bytes
+    constexpr bool TIGHT = S::BS > 512 && 2 * NV * n * (int)sizeof(R) / 4 > 128;
 
     const int tid = threadIdx.x;
     const int lc = tid / NN, a = tid % NN;
@@ -610,8 +612,12 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
                 __asm__ volatile("" ::: "memory");
             }
         }
-        // time contraction in registers: on the matrix unit, or with row s of Kw broadcast from
-        // LDS and shared by the variables
+        // time contraction in registers: on the matrix unit, or with row s of Kw from the scalar cache,
+        // shared by the variables.  Where pencil and flux sums exceed a lane's registers (TIGHT) the sums
+        // come from scratch: one variable's at a time, against the rows two by two.  Left to itself the
+        // compiler keeps the whole operator in scalar registers instead, whose spills cost 1750 lane
+        // reads per sweep (24^3 cells of degree 9 in FP64: 87.6 -> 84.2 ms).  The first sweep's sums are
+        // the same at every time node and stay in registers, so there the rows go one after the other.
         if constexpr (MAT) {
 #pragma unroll
             for (int v = 0; v < NV; v++) {
@@ -620,9 +626,25 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
 #pragma unroll
                 for (int s = 0; s < n; s++) q[v][s] = u0[v] - acc[s / 4][s % 4];
             }
+        } else if constexpr (TIGHT && !FIRST) {
+#pragma unroll
+            for (int v = 0; v < NV; v++) {
+                R acc[n];
+#pragma unroll
+                for (int s = 0; s < n; s++) {
+                    if (s % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+                    const OpPtr<R> row = here(Kw) + s * MAXN;
+                    acc[s] = 0;
+#pragma unroll
+                    for (int t = 0; t < n; t++) acc[s] += row[t] * Sacc[v][t];
+                }
+#pragma unroll
+                for (int s = 0; s < n; s++) q[v][s] = u0[v] - acc[s];
+            }
         } else {
 #pragma unroll
             for (int s = 0; s < n; s++) {
+                if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
                 const OpPtr<R> row = here(Kw) + s * MAXN;
                 R acc[NV];
 #pragma unroll

@@ -100,3 +100,9 @@ def test_corrector_of_large_cells_spills_nothing(built, real):
     name = [k for k in built if k.startswith(f"_ZN3adg18k_corrector_detectILi3ELi9E{real}E")]
     assert len(name) == 1 and built[name[0]][".vgpr_spill_count"] == 0
     assert built[name[0]][".sgpr_spill_count"] < 380
+
+
+def test_predictor_3d_degree_9_fp64_time_operator_not_held(built):
+    """The time operator's 10 x 10 entries take 200 scalar registers, twice what a wave has: fewer
+    spilled ones show that they are loaded row by row."""
+    assert predictor(built, 3, 9, "fp64")[".sgpr_spill_count"] < 200
