@@ -54,6 +54,8 @@ struct PredShape {
     static constexpr int CPB = NN <= TB ? TB / NN : 1;
     static constexpr int ACT = CPB * NN;                           // active point owners
     static constexpr int BS = ((ACT + 63) / 64) * 64;
+    // pencil and flux sums exceed the 128 registers that a workgroup of more than 512 threads leaves a lane
+    static constexpr bool TIGHT = BS > 512 && 2 * NV * n * (int)sizeof(R) / 4 > 128;
     // variables per LDS chunk: all where they fit 80 KB, half of a CU's LDS (a second chunk makes the
     // pencils indexed arrays, which live in scratch: 2D N = 8 FP64, 70 KB, in chunks of three of its
     // four variables 4.11 ms on 128 x 128 cells, in one 0.93 ms); else as many as 64 KB hold
@@ -407,8 +409,6 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
     __shared__ R Dvs[n][MAXN], ws[MAXN], Bs[2][MAXN];
     // the spatial contractions use the even / odd form where it saves work (n >= 6)
     constexpr bool EO = n >= 6;
-    // workgroups of more than 512 threads leave a lane 128 registers of 4 bytes
-    constexpr bool TIGHT = S::BS > 512 && 2 * NV * n * (int)sizeof(R) / 4 > 128;
 
     const int tid = threadIdx.x;
     const int lc = tid / NN, a = tid % NN;
@@ -626,7 +626,7 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
 #pragma unroll
                 for (int s = 0; s < n; s++) q[v][s] = u0[v] - acc[s / 4][s % 4];
             }
-        } else if constexpr (TIGHT && !FIRST) {
+        } else if constexpr (S::TIGHT && !FIRST) {
 #pragma unroll
             for (int v = 0; v < NV; v++) {
                 R acc[n];
@@ -644,7 +644,7 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
         } else {
 #pragma unroll
             for (int s = 0; s < n; s++) {
-                if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (S::TIGHT) __builtin_amdgcn_sched_barrier(0);
                 const OpPtr<R> row = here(Kw) + s * MAXN;
                 R acc[NV];
 #pragma unroll
