@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -1299,10 +1300,11 @@ static int batch_enqueue(adg_batch *b, int g, bool timed) {
 }
 
 static int batch_capture(adg_batch *b) {
-    // entries of both parities from the problems' current buffers
+    // entries of both parities from the problems' current buffers; they live until the copies are made
+    std::deque<std::vector<BatchEntry>> sources;
     for (const auto &K : b->cls) {
         for (int g = 0; g < 2; g++) {
-            std::vector<BatchEntry> ents;
+            std::vector<BatchEntry> &ents = sources.emplace_back();
             for (int m : K.members) ents.push_back(batch_entry(b->ps[m], g, b->cfl, b->precision));
             HIPCHK(hipMemcpyAsync(b->ws + K.off_ents[g], ents.data(), sizeof(BatchEntry) * ents.size(),
                                   hipMemcpyHostToDevice, b->stream));
