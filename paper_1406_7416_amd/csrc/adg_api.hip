@@ -362,7 +362,7 @@ int adg_create(const adg_grid_desc *g, int N, double gamma, const adg_params *p,
         }
         P.ncell *= P.nc[k];
     }
-    if (P.ncell > (int64_t)1 << 31) {
+    if (P.ncell >= (int64_t)1 << 31) {   // cell lists and their counts hold int
         delete pb;
         return fail(ADG_EINVAL, "too many cells");
     }
