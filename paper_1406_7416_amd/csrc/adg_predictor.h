@@ -116,7 +116,8 @@ struct PredLds {
 };
 // The line that thread i contracts along axis k (cell * n^d + j), one per thread.  Matrix-unit
 // form: ordered so that every 16 threads take lines of different bank pairs as far as there are
-// any left (neighbouring lines along x are n nodes apart, 2 to 8 of 16 in the same bank pair).
+// any left (neighbouring lines along x are n nodes apart, 2 to 8 of 16 in the same bank pair).  3D
+// N = 9 holds one variable at a time, in 4-byte accesses that this order is not made for.
 template <int DIM, int N, int CPB, int VC, typename R>
 struct LineMap {
     static constexpr int NN = cpow(N + 1, DIM), ACT = CPB * NN;
@@ -592,11 +593,11 @@ __device__ __forceinline__ void pred_cells(const PredArgs<R> &A, double gamma_d,
                 if (act) {
 #pragma unroll
                     for (int t = 0; t < n; t++) {
-                        // one time node after the other: read ahead, the contracted values of a long
+                        // one time node after the other: read ahead, the contracted values of the longest
                         // deviation pencil push its flux sums into scratch (2D N = 9: 57 -> 48 registers
-                        // spilled, 18 fewer in a sweep; vortex, 128 x 128 cells, steps of 1066 -> 1035 us;
-                        // n = 8 spills none there and is 1 % slower with it)
-                        if constexpr (DEV && DIM == 2 && n >= 9 && !FIRST) __builtin_amdgcn_sched_barrier(0);
+                        // spilled, 18 fewer in a sweep; vortex, 128 x 128 cells, steps of 1066 -> 1037 us;
+                        // N = 8 gains 1 % there and loses 2 % on 17 x 17 cells, N = 7 loses 1 %)
+                        if constexpr (DEV && DIM == 2 && n >= 10 && !FIRST) __builtin_amdgcn_sched_barrier(0);
                         lds_get<L, VC>(Xc, pt + L::SS * (FIRST ? 0 : t), [&](int vv, R xk) __attribute__((always_inline)) {
                             if (v0 + vv < NV)
                                 Sacc[v0 + vv][t] = (k == 0) ? ck * xk : Sacc[v0 + vv][t] + ck * xk;

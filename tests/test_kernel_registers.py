@@ -84,12 +84,11 @@ def test_predictor_2d_fp64_pencils_in_registers(built, N):
     assert predictor(built, 2, N, "fp64")[".private_segment_fixed_size"] < 4 * (N + 1) * WIDTH["fp64"]
 
 
-@pytest.mark.parametrize("N", [7, 8, 9])
-def test_predictor_2d_deviation_form_sweep_in_registers(built, N):
+def test_predictor_2d_degree_9_deviation_form_sweep_in_registers(built):
     """A lane's 128 registers hold the pencil and the flux sums of a 2D node in the deviation form
     (2 x 4 x 10 values); what is spilled are the values formed once per cell or kernel besides
-    them, fewer than 50 (57 with the flux sums of N = 9 among them)."""
-    assert predictor(built, 2, N, "dev")[".vgpr_spill_count"] < 50
+    them, fewer than 50 (57 with flux sums among them)."""
+    assert predictor(built, 2, 9, "dev")[".vgpr_spill_count"] < 50
 
 
 @pytest.mark.parametrize("real", ["d", "f"])
