@@ -74,7 +74,8 @@ typedef struct {
     double state[2][5];
 } adg_bc;
 
-/* Uniform Cartesian grid on [lo, hi] with n[k] cells along axis k (k < dim). */
+/* Uniform Cartesian grid on [lo, hi] with n[k] cells along axis k (k < dim), at most 2^30 along an
+ * axis and fewer than 2^31 in all. */
 typedef struct {
     int dim;              /* 2 or 3 */
     int64_t n[3];
